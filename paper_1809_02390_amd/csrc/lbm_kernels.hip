@@ -304,33 +304,60 @@ template <class St>
 using StepTile = typename StepTileOf<St>::type;
 using MomTile = TileShape<64, 16, 4>;
 
-// Tile order across the eight XCDs of the chip: workgroups are dealt to the
-// XCDs round-robin by dispatch index, so dispatch b runs on XCD b % 8.  Give
-// each XCD one contiguous run of tiles (in raster order) so that the tiles
-// whose halo lines overlap share that XCD's L2.  A bijection onto
-// [0, ntiles) for any ntiles.
-__device__ __forceinline__ int xcd_tile(int b, int ntiles) {
-  const int q = ntiles >> 3, r = ntiles & 7, xcd = b & 7, local = b >> 3;
-  return xcd * q + (xcd < r ? xcd : r) + local;
+// Division by a launch constant d (d >= 1): quotients of n < 2^31 from one
+// high multiplication by m = floor(2^32 / d) (2^32 - 1 for d = 1), at most
+// one too small, and a correction.
+struct Divisor {
+  unsigned d, m;
+};
+inline Divisor make_divisor(unsigned d) { return {d, d == 1 ? 0xFFFFFFFFu : (unsigned)((1ull << 32) / d)}; }
+__device__ __forceinline__ unsigned div_mod(unsigned n, const Divisor& v, unsigned& rem) {
+  unsigned q = (unsigned)(((unsigned long long)n * v.m) >> 32), r = n - q * v.d;
+  if (r >= v.d) r -= v.d, ++q;
+  rem = r;
+  return q;
 }
 
-// Position (tx, ty) of the tile with order index t when the tiles are
-// visited in vertical strips of `strip` tile columns (1 <= strip <= ntx),
-// band by band within a strip: the tile that shares a halo line with the
-// tile above it comes `strip` tiles later, whatever the lattice width, so
-// the line is still in L2 when it is read again.  A bijection for any ntx,
-// nty.
-__device__ __forceinline__ void strip_tile(int t, int ntx, int nty, int strip, int& tx, int& ty) {
-  const int full = ntx / strip, per = strip * nty;  // full strips first, then a narrower one
-  if (t < full * per) {
-    const int s = t / per, rem = t - s * per;
-    ty = rem / strip;
-    tx = s * strip + (rem - ty * strip);
-  } else {
-    const int w = ntx - full * strip, rem = t - full * per;
-    ty = rem / w;
-    tx = full * strip + (rem - ty * w);
-  }
+// Order in which a launch visits the tiles of an ntx x nty grid.
+//
+// Across the eight XCDs of the chip: workgroups are dealt to the XCDs
+// round-robin by dispatch index, so dispatch b runs on XCD b % 8.  Each XCD
+// gets one contiguous run of the order, so that the tiles whose halo lines
+// overlap share that XCD's L2.
+//
+// Within the order: vertical strips of `strip` tile columns (1 <= strip <=
+// ntx), band by band within a strip; the tile that shares a halo line with
+// the tile above it comes `strip` tiles later, whatever the lattice width,
+// so the line is still in L2 when it is read again.  Full strips first, then
+// a narrower one.  The host passes the divisors (Divisor), so that a wave
+// reaches its first load after about 30 scalar instructions and one round of
+// scalar loads; dividing in the kernel took about 150, a latency in front of
+// the loads of every workgroup.  Measured, us per step before and after:
+// two-step kernel 44.0 / 40.8 at 2048^2, 152 / 151 at 4096^2; one-step FP32
+// 206 / 199 and FP16 176 / 170 at 4096^2, FP16 53.0 / 48.6 at 2048^2;
+// adjoint 9.34 / 9.01 at 512^2, 108 / 105.5 at 2048^2, 402 / 396 at 4096^2.
+struct TileOrder {
+  unsigned xq, xr;            // tiles / 8, tiles % 8
+  unsigned full;              // full strips
+  Divisor per, strip, last;   // tiles per full strip; its columns; columns of the narrower strip
+};
+inline TileOrder make_order(int ntx, int nty, int strip) {
+  const unsigned n = (unsigned)ntx * nty, w = (unsigned)(ntx % strip);
+  return {n >> 3, n & 7, (unsigned)(ntx / strip), make_divisor((unsigned)strip * nty), make_divisor((unsigned)strip),
+          make_divisor(w ? w : 1)};
+}
+
+// Tile (tx, ty) of dispatch b: a bijection onto the grid for any ntx, nty.
+// Without branches, so that the launch constants arrive in one round of
+// scalar loads.
+__device__ __forceinline__ void order_tile(unsigned b, const TileOrder& o, int& tx, int& ty) {
+  const unsigned xcd = b & 7, t = xcd * o.xq + (xcd < o.xr ? xcd : o.xr) + (b >> 3);
+  unsigned rem, c;
+  const unsigned s = div_mod(t, o.per, rem);
+  const bool narrow = s >= o.full;
+  const Divisor v = {narrow ? o.last.d : o.strip.d, narrow ? o.last.m : o.strip.m};
+  ty = (int)div_mod(rem, v, c);
+  tx = (int)(s * o.strip.d + c);
 }
 
 // Coordinates (hx, hy) in the (TY+2) x LW density tile of ring slot t:
@@ -477,13 +504,13 @@ __device__ __forceinline__ void neighbours(const float* srho, int hx, int hy, fl
 }
 
 // Step kernel: one tile per workgroup, tiles ordered across the XCDs by
-// xcd_tile so that neighbouring tiles (whose halo lines overlap) run on the
+// order_tile so that neighbouring tiles (whose halo lines overlap) run on the
 // same XCD and share its L2.
 template <class S, class St, int kMode = kAbs>
 __global__ __launch_bounds__(S::NTHREADS) void step_kernel(const void* __restrict__ src, void* __restrict__ dst,
                                                            const uint16_t* __restrict__ ref_in,
-                                                           uint16_t* __restrict__ ref_out, int nx, int ny, int ntx,
-                                                           int ntiles, int strip, Coef<float> c, RefPoly<float> q,
+                                                           uint16_t* __restrict__ ref_out, int nx, int ny,
+                                                           TileOrder order, Coef<float> c, RefPoly<float> q,
                                                            TileRows rows) {
   using E = typename St::E;
   __shared__ float srho[S::LDS];
@@ -491,7 +518,7 @@ __global__ __launch_bounds__(S::NTHREADS) void step_kernel(const void* __restric
   const Layout L = state_layout(nx, ny, St::ES);
   const size_t N = L.ps, rowb = (size_t)St::ES * L.rp;
   int tx, ty;
-  strip_tile(xcd_tile(blockIdx.x, ntiles), ntx, ntiles / ntx, strip, tx, ty);
+  order_tile(blockIdx.x, order, tx, ty);
   const int x0 = tx * S::TX, y0 = tile_row(rows, ty) * S::TY;
   float f[S::NPT][9];
   float rho[S::NPT];
@@ -614,8 +641,8 @@ __device__ __forceinline__ void push_node(const float* f, int X, int Y, float* s
 
 template <class S, bool kMid>
 __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restrict__ src, float* __restrict__ mid,
-                                                            float* __restrict__ dst, int nx, int ny, int ntx,
-                                                            int ntiles, int strip, Coef<float> c) {
+                                                            float* __restrict__ dst, int nx, int ny,
+                                                            TileOrder order, Coef<float> c) {
   __shared__ float s1[S::W1 * S::H1];  // densities at t of the loaded region; then at t + 1 of tile + ring
   __shared__ float sg[9 * S::G];       // populations arriving at the tile and its ring at t + 1
   const size_t rowb = (size_t)36 * nx;  // bytes from one lattice row of a state to the next
@@ -623,7 +650,7 @@ __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restr
   // one population of a row to the next
   const unsigned rb = 36u * (unsigned)nx, pb = 4u * (unsigned)nx;
   int tx, ty;
-  strip_tile(xcd_tile(blockIdx.x, ntiles), ntx, ntiles / ntx, strip, tx, ty);
+  order_tile(blockIdx.x, order, tx, ty);
   const int x0 = tx * S::TX, y0 = ty * S::TY;
   const int lx = threadIdx.x, ly = threadIdx.y, tid = ly * S::TX + lx;
   // side node of this thread: column sc of the six outside the tile's columns
@@ -1120,14 +1147,14 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_step_kernel(const float* 
                                                                    const float* __restrict__ adj_in,
                                                                    float* __restrict__ adj_out,
                                                                    double* __restrict__ partials, int nx, int ny,
-                                                                   int ntx, int ntiles, int strip, Coef<float> c,
+                                                                   TileOrder order, Coef<float> c,
                                                                    TileRows rows) {
   using L = AdjLds<S>;
   __shared__ float srho[S::LDS];
   __shared__ float snu[S::LDS];
   __shared__ __align__(8) float sa[L::NSA];
   int tx, ty;
-  strip_tile(xcd_tile(blockIdx.x, ntiles), ntx, ntiles / ntx, strip, tx, ty);
+  order_tile(blockIdx.x, order, tx, ty);
   const int x0 = tx * S::TX, y0 = tile_row(rows, ty) * S::TY;
   float th[3] = {0.0f, 0.0f, 0.0f};
   if constexpr (kMode == kWide)  // the tile rows that wrap: never interior
@@ -1371,7 +1398,7 @@ namespace {
 template <class S>
 int tiles_x(int nx) { return (nx + S::TX - 1) / S::TX; }
 
-// Tile columns per strip of the tile order (strip_tile) for tiles tx nodes
+// Tile columns per strip of the tile order (TileOrder) for tiles tx nodes
 // wide on a lattice nx nodes wide.  Measured on MI355X for the FP32 step and
 // the adjoint, which stream their bytes from HBM: raster order up to 2048
 // nodes, beyond that strips a quarter of the lattice wide and at least 1024
@@ -1428,7 +1455,7 @@ void launch_step_tiles(const lbm_ctx* ctx, const void* src, void* dst, const uin
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
   for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
     step_kernel<S, St, decltype(mode)::value><<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-        src, dst, ref_in, ref_out, nx, ny, ntx, ntx * nrows, strip_width(nx, S::TX, St::kRef), ctx->c, ctx->q,
+        src, dst, ref_in, ref_out, nx, ny, make_order(ntx, nrows, strip_width(nx, S::TX, St::kRef)), ctx->c, ctx->q,
         rows);
   });
 }
@@ -1484,8 +1511,8 @@ template <class S, bool kMid>
 void launch_step2_on(const lbm_ctx* ctx, const void* src, void* mid, void* dst) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
   step2_kernel<S, kMid><<<nt, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-      static_cast<const float*>(src), static_cast<float*>(mid), static_cast<float*>(dst), nx, ny, ntx, nt,
-      strip_width(nx, S::TX, false), ctx->c);
+      static_cast<const float*>(src), static_cast<float*>(mid), static_cast<float*>(dst), nx, ny,
+      make_order(ntx, nt / ntx, strip_width(nx, S::TX, false)), ctx->c);
 }
 template <bool kMid>
 void launch_step2(const lbm_ctx* ctx, const void* src, void* mid, void* dst) {
@@ -1862,7 +1889,7 @@ static void launch_adjoint(const lbm_ctx* ctx, const void* f_t, const void* adj_
   for_tile_rows<S, true>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
     adjoint_step_kernel<S, decltype(mode)::value><<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
         static_cast<const float*>(f_t), static_cast<const float*>(adj_next), static_cast<float*>(adj_out),
-        ctx->theta, nx, ny, ntx, ntx * nrows, strip_width(nx, S::TX, false), ctx->c, rows);
+        ctx->theta, nx, ny, make_order(ntx, nrows, strip_width(nx, S::TX, false)), ctx->c, rows);
   });
 }
 
