@@ -132,6 +132,16 @@ __device__ __forceinline__ E ldb(const char* __restrict__ base, unsigned off) {
   return *reinterpret_cast<const E*>(base + off);
 }
 
+// Store that is left in the caches (kStream false) or streamed past them.
+template <bool kStream, typename E>
+__device__ __forceinline__ void put(E v, char* base, unsigned off) {
+  E* p = reinterpret_cast<E*>(base + off);
+  if constexpr (kStream)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
 template <typename E>
 struct Planes {
   const char* p[9];
@@ -336,28 +346,39 @@ __device__ __forceinline__ unsigned div_mod(unsigned n, const Divisor& v, unsign
 // two-step kernel 44.0 / 40.8 at 2048^2, 152 / 151 at 4096^2; one-step FP32
 // 206 / 199 and FP16 176 / 170 at 4096^2, FP16 53.0 / 48.6 at 2048^2;
 // adjoint 9.34 / 9.01 at 512^2, 108 / 105.5 at 2048^2, 402 / 396 at 4096^2.
+//
+// Launches whose stores stay in the caches (stream_stores) alternate between
+// the order and its reverse within each XCD: the next launch then starts on
+// what the last one wrote last, which the caches still hold.  Measured, us
+// per step, one order / alternating: two-step kernel 42.4 / 40.7 at 2048^2,
+// 89.9 / 87.3 at 3000^2; FP16 163.5 / 158.0 at 4000^2; adjoint 116 / 109 at
+// 2050 x 2047.
 struct TileOrder {
   unsigned xq, xr;            // tiles / 8, tiles % 8
+  unsigned reverse;           // 1: each XCD's run backwards
   unsigned full;              // full strips
   Divisor per, strip, last;   // tiles per full strip; its columns; columns of the narrower strip
 };
-inline TileOrder make_order(int ntx, int nty, int strip) {
+inline TileOrder make_order(int ntx, int nty, int strip, bool reverse) {
   const unsigned n = (unsigned)ntx * nty, w = (unsigned)(ntx % strip);
-  return {n >> 3, n & 7, (unsigned)(ntx / strip), make_divisor((unsigned)strip * nty), make_divisor((unsigned)strip),
-          make_divisor(w ? w : 1)};
+  return {n >> 3, n & 7, reverse ? 1u : 0u, (unsigned)(ntx / strip), make_divisor((unsigned)strip * nty),
+          make_divisor((unsigned)strip), make_divisor(w ? w : 1)};
 }
 
 // Tile (tx, ty) of dispatch b: a bijection onto the grid for any ntx, nty.
 // Without branches, so that the launch constants arrive in one round of
-// scalar loads.
-__device__ __forceinline__ void order_tile(unsigned b, const TileOrder& o, int& tx, int& ty) {
-  const unsigned xcd = b & 7, t = xcd * o.xq + (xcd < o.xr ? xcd : o.xr) + (b >> 3);
+// scalar loads.  Returns the dispatch that visits the tile in the forward
+// order: one number per tile, whichever way the launch runs.
+__device__ __forceinline__ unsigned order_tile(unsigned b, const TileOrder& o, int& tx, int& ty) {
+  const unsigned xcd = b & 7, last = o.xq - (xcd < o.xr ? 0u : 1u), l = o.reverse ? last - (b >> 3) : b >> 3;
+  const unsigned t = xcd * o.xq + (xcd < o.xr ? xcd : o.xr) + l;
   unsigned rem, c;
   const unsigned s = div_mod(t, o.per, rem);
   const bool narrow = s >= o.full;
   const Divisor v = {narrow ? o.last.d : o.strip.d, narrow ? o.last.m : o.strip.m};
   ty = (int)div_mod(rem, v, c);
   tx = (int)(s * o.strip.d + c);
+  return l << 3 | xcd;
 }
 
 // Coordinates (hx, hy) in the (TY+2) x LW density tile of ring slot t:
@@ -506,7 +527,7 @@ __device__ __forceinline__ void neighbours(const float* srho, int hx, int hy, fl
 // Step kernel: one tile per workgroup, tiles ordered across the XCDs by
 // order_tile so that neighbouring tiles (whose halo lines overlap) run on the
 // same XCD and share its L2.
-template <class S, class St, int kMode = kAbs>
+template <class S, class St, int kMode, bool kStream>
 __global__ __launch_bounds__(S::NTHREADS) void step_kernel(const void* __restrict__ src, void* __restrict__ dst,
                                                            const uint16_t* __restrict__ ref_in,
                                                            uint16_t* __restrict__ ref_out, int nx, int ny,
@@ -567,7 +588,7 @@ __global__ __launch_bounds__(S::NTHREADS) void step_kernel(const void* __restric
       *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ref_out) + 2u * ((unsigned)y * nx + (unsigned)x)) =
           f32_to_f16(nb[0]);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(out[i], reinterpret_cast<E*>(Q.p[i] + o));
+    for (int i = 0; i < 9; ++i) put<kStream>(out[i], Q.p[i], o);
   }
 }
 
@@ -591,7 +612,8 @@ __global__ __launch_bounds__(S::NTHREADS) void step_kernel(const void* __restric
 // workgroups per CU; measured at 4096^2 against 64 x 16 in 256 or 512
 // threads, 32 x 32, 64 x 20, 64 x 32, 128 x 16 and other thread counts).
 // kMid also stores the state of t + 1 (the checkpoint driver keeps every
-// state).
+// state), past the caches: no launch reads it soon (1100^2, us per step,
+// streamed / cached: 17.5 / 18.6; 2050 x 2048 61.2 / 64.5).
 // ---------------------------------------------------------------------------
 template <int TX_, int TY_, int WY_>
 struct Tile2Shape {
@@ -639,7 +661,7 @@ __device__ __forceinline__ void push_node(const float* f, int X, int Y, float* s
   }
 }
 
-template <class S, bool kMid>
+template <class S, bool kMid, bool kStream>
 __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restrict__ src, float* __restrict__ mid,
                                                             float* __restrict__ dst, int nx, int ny,
                                                             TileOrder order, Coef<float> c) {
@@ -756,24 +778,25 @@ __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restr
       const unsigned o = (unsigned)r * rb + 4u * (unsigned)x;
 #pragma unroll
       for (int i = 0; i < 9; ++i)
-        __builtin_nontemporal_store(sg[i * S::G + pos + kCy[i] * S::LW + kCx[i]], reinterpret_cast<float*>(mb + i * pb + o));
+        put<true>(sg[i * S::G + pos + kCy[i] * S::LW + kCx[i]], mb + i * pb, o);
     }
     float gx, gy;
     stencil_at<S::LW>(s2, (r + 1) * S::LW + lx + 1, gx, gy);
     collide_node<float>(fd[k], rd[k], gx, gy, c);
     const unsigned o = (unsigned)r * rb + 4u * (unsigned)x;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(fd[k][i], reinterpret_cast<float*>(ob + i * pb + o));
+    for (int i = 0; i < 9; ++i) put<kStream>(fd[k][i], ob + i * pb, o);
   }
 }
 
-// Deterministic FP64 sum of three per-thread values over a block, into this
-// block's slot partials[3 b .. 3 b + 2] (added to it if kAdd, else stored):
+// Deterministic FP64 sum of three per-thread values over a block, into the
+// slot partials[3 slot .. 3 slot + 2] (added to it if kAdd, else stored):
 // a fixed shuffle tree inside each wave, then the waves' sums in wave order.
 // red holds 3 doubles per wave of LDS; it may alias LDS the block read
 // before the call.
 template <class S, bool kAdd>
-__device__ __forceinline__ void block_sum3(const double* in, double* red, double* __restrict__ partials) {
+__device__ __forceinline__ void block_sum3(const double* in, double* red, double* __restrict__ partials,
+                                           unsigned slot) {
   constexpr int NW = S::NTHREADS / 64;
   const int tid = threadIdx.y * S::TX + threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double v[3] = {in[0], in[1], in[2]};
@@ -790,9 +813,9 @@ __device__ __forceinline__ void block_sum3(const double* in, double* red, double
     double s = red[tid * NW];
     for (int w = 1; w < NW; ++w) s += red[tid * NW + w];
     if constexpr (kAdd)
-      partials[(size_t)blockIdx.x * 3 + tid] += s;
+      partials[(size_t)slot * 3 + tid] += s;
     else
-      partials[(size_t)blockIdx.x * 3 + tid] = s;
+      partials[(size_t)slot * 3 + tid] = s;
   }
 }
 
@@ -837,7 +860,7 @@ __global__ __launch_bounds__(MomTile::NTHREADS) void moments_kernel(
     sy += (double)m[5];
   }
   const double v[3] = {sm, sx, sy};
-  block_sum3<S, false>(v, sred, partials);
+  block_sum3<S, false>(v, sred, partials, blockIdx.x);
 }
 
 // Sum of the per-workgroup partials in a fixed order: each thread adds a
@@ -852,7 +875,7 @@ __global__ __launch_bounds__(RED) void finish_sums(const double* __restrict__ pa
   double a[3] = {0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < nblocks; b += RED)
     for (int k = 0; k < 3; ++k) a[k] += partials[(size_t)b * 3 + k];
-  block_sum3<FlatBlock, false>(a, red, out);  // one block: its slot is out[0..2]
+  block_sum3<FlatBlock, false>(a, red, out, 0);  // one block: its slot is out[0..2]
 }
 
 // Store the post-streaming populations f of node (x, y) into the pull
@@ -1053,20 +1076,21 @@ __device__ __forceinline__ void stage_nu(const float* __restrict__ ax, const flo
   put_nu<S>(h, sa, snu);
 }
 
-// Deterministic FP64 block sum of three per-thread FP32 values, added to this
-// block's slot of partials (a block always owns the same slot, so sums over
-// many launches are reproducible bit for bit).
+// Deterministic FP64 block sum of three per-thread FP32 values, added to a
+// slot of partials (a tile always adds to the same slot, so sums over many
+// launches are reproducible bit for bit).
 template <class S>
-__device__ __forceinline__ void block_accumulate(const float* th, double* red, double* __restrict__ partials) {
+__device__ __forceinline__ void block_accumulate(const float* th, double* red, double* __restrict__ partials,
+                                                 unsigned slot) {
   const double v[3] = {(double)th[0], (double)th[1], (double)th[2]};
-  block_sum3<S, true>(v, red, partials);
+  block_sum3<S, true>(v, red, partials, slot);
 }
 
 // One tile of the adjoint step (kInterior: interior_tile holds, no wrap).
 // Every global load (the forward populations with their ring, the A halo and
 // the adjoint populations of the own nodes) is issued before the first
 // barrier.
-template <class S, bool kInterior, int kMode>
+template <class S, bool kInterior, int kMode, bool kStream>
 __device__ __forceinline__ void adjoint_tile(const float* __restrict__ fsrc, const float* __restrict__ adj_in,
                                              float* __restrict__ adj_out, int nx, int ny, int x0, int y0,
                                              const Coef<float>& c, float* srho, float* snu, float* sa, float* th) {
@@ -1136,13 +1160,13 @@ __device__ __forceinline__ void adjoint_tile(const float* __restrict__ fsrc, con
     const unsigned o = o0 + (unsigned)(k * S::WY) * rb;
     // uniform field bases and one 32-bit lane offset for the eleven stores
 #pragma unroll
-    for (int i = 0; i < 9; ++i) __builtin_nontemporal_store(lf[i], reinterpret_cast<float*>(Q.p[i] + o));
-    __builtin_nontemporal_store(agx, reinterpret_cast<float*>(Q.p[9] + o));
-    __builtin_nontemporal_store(agy, reinterpret_cast<float*>(Q.p[10] + o));
+    for (int i = 0; i < 9; ++i) put<kStream>(lf[i], Q.p[i], o);
+    put<kStream>(agx, Q.p[9], o);
+    put<kStream>(agy, Q.p[10], o);
   }
 }
 
-template <class S, int kMode = kAbs>
+template <class S, int kMode, bool kStream>
 __global__ __launch_bounds__(S::NTHREADS) void adjoint_step_kernel(const float* __restrict__ fsrc,
                                                                    const float* __restrict__ adj_in,
                                                                    float* __restrict__ adj_out,
@@ -1154,16 +1178,16 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_step_kernel(const float* 
   __shared__ float snu[S::LDS];
   __shared__ __align__(8) float sa[L::NSA];
   int tx, ty;
-  order_tile(blockIdx.x, order, tx, ty);
+  const unsigned slot = order_tile(blockIdx.x, order, tx, ty);
   const int x0 = tx * S::TX, y0 = tile_row(rows, ty) * S::TY;
   float th[3] = {0.0f, 0.0f, 0.0f};
   if constexpr (kMode == kWide)  // the tile rows that wrap: never interior
-    adjoint_tile<S, false, kWide>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
+    adjoint_tile<S, false, kWide, kStream>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
   else if (interior_tile<S>(x0, y0, nx, ny))
-    adjoint_tile<S, true, kMode>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
+    adjoint_tile<S, true, kMode, kStream>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
   else
-    adjoint_tile<S, false, kMode>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
-  block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials);
+    adjoint_tile<S, false, kMode, kStream>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
+  block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, slot);
 }
 
 // Lambda = L + nu on the tile, then either exported (kInit false) or taken
@@ -1199,7 +1223,7 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_finish_kernel(
       for (int i = 0; i < 9; ++i) out[(size_t)i * N + o] = lam[i];
     }
   }
-  if constexpr (kInit) block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials);
+  if constexpr (kInit) block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, blockIdx.x);
 }
 
 // Adjoint state (adj_layout) from a plain Lambda (planes nx*ny apart):
@@ -1384,6 +1408,7 @@ struct lbm_ctx {
   int64_t t;
   hipStream_t stream;
   int device;
+  bool reverse;      // direction of the last launch with cached stores (with_stores)
   int cus;           // compute units of the device (tile-shape choice)
   int nblocks;       // workgroups of the moments tile grid
   double* scratch;   // nblocks*3 partials, then 3 totals
@@ -1448,15 +1473,62 @@ void for_tile_rows(int nx, int ny, Fn&& fn) {
   fn(std::integral_constant<int, kAbs>{}, TileRows{0, nty, 0}, nty);
 }
 
+// Whether a kernel streams the state it writes (non-temporal stores) or
+// leaves it in the caches.  bytes: the state written; row: bytes of one of
+// its rows; most: the bytes of source and destination together up to which
+// the next launch still finds part of them there.
+//
+// Three ranges, measured with every size between (us per step, streamed /
+// cached; step2 is the two-step kernel, L2 4 MiB on each of 8 XCDs, memory
+// cache 256 MiB):
+//  - up to two thirds of the L2s the end of the launch, which writes them
+//    back, costs more than the next launch gains: step2 512^2 4.0 / 4.25, one
+//    step 640^2 6.2 / 7.5, FP16 1000 x 700 9.6 / 10.6; crossing over at 16 to
+//    21 MB: step2 701 x 700 8.06 / 8.04, 896^2 11.8 / 11.0, one step 701 x
+//    700 10.3 / 11.0, 768^2 12.15 / 12.03, FP16 901 x 900 12.5 / 12.6, 1024^2
+//    13.7 / 13.5;
+//  - rows that do not start on 64 bytes share lines between workgroups, and
+//    cached stores merge them: step2 1100^2 15.9 / 14.1, 4097 x 4093 166 /
+//    159, FP16 4097 x 4093 197 / 180, adjoint 493 / 440;
+//  - else cached while the caches hold enough of it.  The one-step FP32 and
+//    adjoint kernels and the two-step kernel that stores both states, which
+//    HBM bounds, gain while the memory cache holds source and destination
+//    (one step 1792^2 46.0 / 38.6, 2048^2 57.8 / 57.8, 4096^2 199 / 211;
+//    adjoint 1600^2 67.8 / 65.8, 2048^2 109.8 / 110.5; both states 1536^2
+//    32.7 / 31.1, 2048^2 53.3 / 54.3), the kernels the vector ALU bounds up
+//    to about 640 MB (step2 2048^2 42.4 / 40.7, 3000^2 91.3 / 87.3, 4096^2
+//    143.6 / 146; FP16 2048^2 48.9 / 44.9, 4000^2 164 / 158, 8192^2 627 /
+//    634).
+constexpr unsigned long long kCachedFrom = 20ull << 20, kCachedHbm = 288ull << 20, kCachedAlu = 640ull << 20;
+bool stream_stores(unsigned long long bytes, unsigned long long row, unsigned long long most) {
+  if (bytes < kCachedFrom) return true;
+  return row % 64 == 0 && 2 * bytes > most;
+}
+
+// Call fn(stream, reverse) for one launch (or the launches of one step):
+// stream as std::bool_constant, and whether the tiles run backwards, which
+// cached launches do every other time.
+template <class Fn>
+void with_stores(lbm_ctx* ctx, bool stream, Fn&& fn) {
+  if (stream) return fn(std::true_type{}, false);
+  ctx->reverse = !ctx->reverse;
+  fn(std::false_type{}, ctx->reverse);
+}
+
 // One step of storage St with tile shape S from the buffer src (and its
 // reference plane) to dst, on the context's stream.
 template <class St, class S>
-void launch_step_tiles(const lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
+void launch_step_tiles(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
-  for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
-    step_kernel<S, St, decltype(mode)::value><<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-        src, dst, ref_in, ref_out, nx, ny, make_order(ntx, nrows, strip_width(nx, S::TX, St::kRef)), ctx->c, ctx->q,
-        rows);
+  const bool stream = stream_stores((9ull * St::ES + (St::kRef ? 2 : 0)) * nx * ny, (unsigned long long)St::ES * nx,
+                                    St::kRef ? kCachedAlu : kCachedHbm);
+  with_stores(ctx, stream, [&](auto str, bool reverse) {
+    for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
+      step_kernel<S, St, decltype(mode)::value, decltype(str)::value>
+          <<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+              src, dst, ref_in, ref_out, nx, ny,
+              make_order(ntx, nrows, strip_width(nx, S::TX, St::kRef), reverse), ctx->c, ctx->q, rows);
+    });
   });
 }
 
@@ -1469,7 +1541,7 @@ using SmallTile = TileShape<64, 4, 4>;
 using MidTileF32 = TileShape<128, 8, 4>;
 
 template <class St>
-void launch_step(const lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
+void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   if (tiles_total<StepTile<St>>(nx, ny) >= ctx->cus) return launch_step_tiles<St, StepTile<St>>(ctx, src, dst, ref_in, ref_out);
   if constexpr (std::is_same_v<St, StoreF32>)
@@ -1508,14 +1580,16 @@ bool use_step2(const lbm_ctx* ctx) { return step2_shape(ctx) != 0; }
 
 // src (time t) -> dst (time t + 2), and mid (time t + 1) if kMid.
 template <class S, bool kMid>
-void launch_step2_on(const lbm_ctx* ctx, const void* src, void* mid, void* dst) {
+void launch_step2_on(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
-  step2_kernel<S, kMid><<<nt, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-      static_cast<const float*>(src), static_cast<float*>(mid), static_cast<float*>(dst), nx, ny,
-      make_order(ntx, nt / ntx, strip_width(nx, S::TX, false)), ctx->c);
+  with_stores(ctx, stream_stores(36ull * nx * ny, 4ull * nx, kMid ? kCachedHbm : kCachedAlu), [&](auto str, bool reverse) {
+    step2_kernel<S, kMid, decltype(str)::value><<<nt, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+        static_cast<const float*>(src), static_cast<float*>(mid), static_cast<float*>(dst), nx, ny,
+        make_order(ntx, nt / ntx, strip_width(nx, S::TX, false), reverse), ctx->c);
+  });
 }
 template <bool kMid>
-void launch_step2(const lbm_ctx* ctx, const void* src, void* mid, void* dst) {
+void launch_step2(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
   switch (step2_shape(ctx)) {
     case 1: launch_step2_on<Step2Tile, kMid>(ctx, src, mid, dst); break;
     case 2: launch_step2_on<Step2Mid, kMid>(ctx, src, mid, dst); break;
@@ -1883,13 +1957,16 @@ int lbm_adjoint_seed(lbm_ctx* ctx, const float* lam, void* adj) {
 // One adjoint step on the context's stream (split like the forward step for
 // wide FP32 states).  Blocks of both launches add into the partial-sum
 // slots 0 .. grid-1 in launch order, so the sums stay reproducible.
-static void launch_adjoint(const lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
+static void launch_adjoint(lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
   using S = AdjTile;
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
-  for_tile_rows<S, true>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
-    adjoint_step_kernel<S, decltype(mode)::value><<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-        static_cast<const float*>(f_t), static_cast<const float*>(adj_next), static_cast<float*>(adj_out),
-        ctx->theta, nx, ny, make_order(ntx, nrows, strip_width(nx, S::TX, false)), ctx->c, rows);
+  with_stores(ctx, stream_stores(44ull * nx * ny, 4ull * nx, kCachedHbm), [&](auto str, bool reverse) {
+    for_tile_rows<S, true>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
+      adjoint_step_kernel<S, decltype(mode)::value, decltype(str)::value>
+          <<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+              static_cast<const float*>(f_t), static_cast<const float*>(adj_next), static_cast<float*>(adj_out),
+              ctx->theta, nx, ny, make_order(ntx, nrows, strip_width(nx, S::TX, false), reverse), ctx->c, rows);
+    });
   });
 }
 
