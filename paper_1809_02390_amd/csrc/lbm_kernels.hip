@@ -789,6 +789,155 @@ __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restr
   }
 }
 
+// ---------------------------------------------------------------------------
+// Several time steps per launch on small lattices (every storage).  A
+// workgroup advances a TX x TY tile by k <= K steps.  Each thread owns one
+// node of the tile plus a ring of 2 k - 1 nodes, numbered from the inside
+// out: the tile first, then ring after ring.  Per step
+//   (1) the density of every node still valid goes to LDS;
+//   (2) its nodes but the outermost ring collide and push f-bar, encoded as
+//       the storage holds it, to the LDS slots of the nodes it streams to;
+//       tile nodes store f-bar where the caller wants the state;
+//   (3) every node takes its nine populations back.
+// A step shrinks the valid part by two rings (one the stencil reads, one the
+// populations cross), so each phase works on a prefix of the threads and
+// whole waves drop out as it shrinks.  Every node is updated by the
+// operations of step_kernel in the same order, the 2-byte storages rounding
+// every state as it does, so k fused steps give the bits of k single steps.
+//
+// What bounds it: not bandwidth (a whole 256^2 state is 2.4 MB) and not the
+// vector ALU, but one wave's chain of instructions.  A launch costs about
+// 2.8 us before its first collision (the gap between dependent launches, the
+// kernel arguments, the first loads, cold instruction fetch), and a step a
+// further 0.8 us when each SIMD holds one wave (1870 cycles: 1340 for the
+// collision, at one instruction per five cycles, the rest LDS and barriers).
+// So: as many steps per launch as the recomputed rings allow; one node per
+// thread, which spreads the collisions over all SIMDs; and the steps as a
+// loop over one copy of the code, since instructions executed once cost
+// their fetch (a straight line of 2048 takes 3.8 us longer than a loop).
+// ---------------------------------------------------------------------------
+template <int TX_, int TY_, int K_>
+struct TileKShape {
+  static constexpr int TX = TX_, TY = TY_, K = K_, R = 2 * K - 1;
+  static constexpr int W = TX + 2 * R, H = TY + 2 * R, N = W * H;
+  static constexpr int NT = (N + 63) / 64 * 64;
+  static_assert(NT <= 1024, "one node per thread");
+  // nodes of the tile and its first j rings
+  static constexpr __host__ __device__ int prefix(int j) { return (TX + 2 * j) * (TY + 2 * j); }
+};
+
+// Position (X, Y) in the W x H region of thread t < N: ring j around the box
+// of the tile and its first j - 1 rings is the row above the box, the row
+// below, then the column to its left and the one to its right.
+template <class S>
+__device__ __forceinline__ void ring_node(int t, int& X, int& Y) {
+  int j = 0;
+#pragma unroll
+  for (int m = 0; m < S::R; ++m) j += t >= S::prefix(m);
+  const int w = S::TX + 2 * j, h = S::TY + 2 * j - 2, u = t - (w - 2) * h;  // ring: rows of w nodes, columns of h
+  const bool row = u < 2 * w;
+  const int n = row ? w : h, v = row ? u : u - 2 * w;
+  const bool second = v >= n;
+  const int along = second ? v - n : v;  // position along the row or column
+  X = S::R - j + (row ? along : (second ? w - 1 : 0));
+  Y = S::R - j + (row ? (second ? h + 1 : 0) : along + 1);
+  if (j == 0) X = S::R + t % S::TX, Y = S::R + t / S::TX;
+}
+
+// States a launch of k steps writes: p[s] receives the state after step
+// s + 1 (null: not stored).
+template <int K>
+struct StepOuts {
+  void* p[K];
+};
+
+template <class S, class St>
+__global__ __launch_bounds__(S::NT) void stepk_kernel(const void* __restrict__ src, StepOuts<S::K> outs,
+                                                      const uint16_t* __restrict__ ref_in,
+                                                      uint16_t* __restrict__ ref_out, int nx, int ny,
+                                                      TileOrder order, int k, Coef<float> c, RefPoly<float> q) {
+  using E = typename St::E;
+  __shared__ E sf[9 * S::N];                         // populations arriving at each node
+  __shared__ float srho[S::N];                       // densities
+  __shared__ float sref[St::kRef ? 3 * S::N : 1];    // -S f_ref of each velocity class (2-byte storages)
+  const Layout L = state_layout(nx, ny, St::ES);
+  int tx, ty;
+  order_tile(blockIdx.x, order, tx, ty);
+  const int tid = threadIdx.x;
+  int X, Y;
+  ring_node<S>(tid, X, Y);
+  const int x = tx * S::TX - S::R + X, y = ty * S::TY - S::R + Y, pos = Y * S::W + X;
+  const bool own = tid < S::TX * S::TY && x < nx && y < ny;
+  const unsigned off = St::ES * ((unsigned)y * L.rp + (unsigned)x);
+  float f[9], ref[3];
+  // f(t) arriving at the tile and its first 2 k - 1 rings
+  if (tid < (S::TX + 4 * k - 2) * (S::TY + 4 * k - 2)) {
+    const int xw = wrap(x, nx), yw = wrap(y, ny);
+    E r[9];
+    pull_raw<E>(planes<E>(src, L.ps), node_addr<St::ES>(xw, yw, nx, ny, L.rp), r);
+    decode<St>(r, St::kRef ? ref_in[(unsigned)yw * nx + (unsigned)xw] : 0, q, f);
+  }
+#pragma unroll 1
+  for (int s = k - 1, j = 0;; --s, ++j) {  // s steps follow this one
+    // nodes that collide (the tile and 2 s rings), nodes whose density they read (one ring more)
+    const int nc = (S::TX + 4 * s) * (S::TY + 4 * s), nd = (S::TX + 4 * s + 2) * (S::TY + 4 * s + 2);
+    float rho = 0.0f;
+    if (tid < nd) {
+      rho = density(f);
+      srho[pos] = rho;
+      if constexpr (St::kRef) {
+        const float rt = ref_density(rho);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          ref[m] = ref_value(q, m, rt);
+          sref[m * S::N + pos] = -q.scale * ref[m];
+        }
+      }
+    }
+    __syncthreads();
+    if (tid < nc) {
+      float gx, gy;
+      stencil_at<S::W>(srho, pos, gx, gy);
+      collide_node<float, St::kRef>(f, rho, gx, gy, c);
+      E o[9];
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        if constexpr (St::kRef)
+          o[i] = St::from_f32(fmaf(f[i], q.scale, sref[velocity_class(i) * S::N + pos + kCy[i] * S::W + kCx[i]]));
+        else
+          o[i] = f[i];
+      }
+      char* const out = static_cast<char*>(outs.p[j]);
+      if (out && own) {
+        // rows of whole 128-byte lines are streamed (every state of 256^2
+        // stored: 2.37 us per step against 2.52), shorter ones left to merge
+        // in the caches (16 x 16 tiles, 620^2: 7.6 against 11.6)
+#pragma unroll
+        for (int i = 0; i < 9; ++i) put<S::TX * sizeof(E) >= 128>(o[i], out + (size_t)i * L.ps * St::ES, off);
+        if constexpr (St::kRef)
+          if (s == 0) ref_out[(unsigned)y * nx + (unsigned)x] = f32_to_f16(rho);
+      }
+      if (s > 0) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) sf[i * S::N + pos + kCy[i] * S::W + kCx[i]] = o[i];
+      }
+    }
+    if (s == 0) break;
+    __syncthreads();
+    // the part still valid: the tile and 2 s - 1 rings.  The next barrier
+    // separates these reads from the next step's pushes.
+    if (tid < (S::TX + 4 * s - 2) * (S::TY + 4 * s - 2)) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        if constexpr (St::kRef)
+          f[i] = fmaf(St::to_f32(sf[i * S::N + pos]), q.inv_scale, ref[velocity_class(i)]);
+        else
+          f[i] = sf[i * S::N + pos];
+      }
+    }
+  }
+}
+
 // Deterministic FP64 sum of three per-thread values over a block, into the
 // slot partials[3 slot .. 3 slot + 2] (added to it if kAdd, else stored):
 // a fixed shuffle tree inside each wave, then the waves' sums in wave order.
@@ -1550,33 +1699,22 @@ void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_i
   launch_step_tiles<St, SmallTile>(ctx, src, dst, ref_in, ref_out);
 }
 
-// Two FP32 steps per launch (step2_kernel) on the largest of three tiles
-// that gives at least one tile per CU: 64 x 24, else 64 x 16, else 32 x 8.
-// On the small lattices of the last two a step lasts a few microseconds and
-// the launches set the pace, so half the launches outweigh the larger share
-// of recomputed ring nodes.  Measured, time per step against single steps:
-// 256^2 2.92 against 3.61 us (32 x 8; 64 x 16: 3.93), 512^2 4.14 against
-// 5.37 us (64 x 16; 32 x 8: 4.68); 32 x 16 and 64 x 8 were no faster.  The
-// tiles address TY + 8 rows of 36 nx bytes from one base with 32-bit
-// offsets, which bounds the width (about 3.7M nodes); wider lattices take
-// single steps.
+// Two FP32 steps per launch (step2_kernel), on lattices too large for
+// stepk_kernel: tiles of 64 x 24, or of 64 x 16 where those come to one per
+// CU (512^2, us per step: 4.02 against 4.52 for stepk_kernel).  The tiles
+// address TY + 8 rows of 36 nx bytes from one base with 32-bit offsets,
+// which bounds the width (about 3.7M nodes); wider lattices take single
+// steps.
 #ifndef LBM_FUSE_STEPS
 #define LBM_FUSE_STEPS 1
 #endif
 using Step2Mid = Tile2Shape<64, 16, 8>;
-using Step2Small = Tile2Shape<32, 8, 8>;
-static_assert(Step2Mid::TY <= Step2Tile::TY && Step2Small::TY <= Step2Tile::TY,
-              "the width bound of the large tile covers the others");
+static_assert(Step2Mid::TY <= Step2Tile::TY, "the width bound of the large tile covers the other");
 
-// 0: single steps; 1, 2, 3: two steps on Step2Tile, Step2Mid, Step2Small.
-int step2_shape(const lbm_ctx* ctx) {
-  const int nx = ctx->p.nx, ny = ctx->p.ny;
-  const unsigned long long band = 36ull * (unsigned long long)nx * (Step2Tile::TY + 8);
-  if (!LBM_FUSE_STEPS || ctx->p.storage != LBM_FP32 || band >= (1ull << 32)) return 0;
-  if (tiles_total<Step2Tile>(nx, ny) >= ctx->cus) return 1;
-  return tiles_total<Step2Mid>(nx, ny) >= ctx->cus ? 2 : 3;
+bool use_step2(const lbm_ctx* ctx) {
+  const unsigned long long band = 36ull * (unsigned long long)ctx->p.nx * (Step2Tile::TY + 8);
+  return LBM_FUSE_STEPS && ctx->p.storage == LBM_FP32 && band < (1ull << 32);
 }
-bool use_step2(const lbm_ctx* ctx) { return step2_shape(ctx) != 0; }
 
 // src (time t) -> dst (time t + 2), and mid (time t + 1) if kMid.
 template <class S, bool kMid>
@@ -1588,13 +1726,78 @@ void launch_step2_on(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
         make_order(ntx, nt / ntx, strip_width(nx, S::TX, false), reverse), ctx->c);
   });
 }
+// k steps of storage St per launch on small lattices (stepk_kernel).
+using StepKTiny = TileKShape<4, 4, 4>;
+using StepKSmall = TileKShape<8, 8, 4>;
+using StepKWide = TileKShape<32, 8, 3>;
+using StepKLast = TileKShape<16, 16, 2>;
+
+// Whether a lattice has just enough 64 x 16 tiles for the two-step kernel to
+// run one per CU (7/8 of the CUs to all of them).
+bool one_mid_tile_per_cu(const lbm_ctx* ctx) {
+  const int t = tiles_total<Step2Mid>(ctx->p.nx, ctx->p.ny);
+  return t <= ctx->cus && 8 * t > 7 * ctx->cus;
+}
+
+// The tile of stepk_kernel (1 .. 4, in the order above), or 0 where the
+// other kernels are faster.  The more steps per launch, the smaller the tile
+// has to be for one thread per node of it and its rings; a tile is taken
+// while the lattice gives the CUs one (4 x 4) or two of them.  Measured, us
+// per step, 4 x 4 / 8 x 8 / 32 x 8 / 16 x 16 tiles / without stepk_kernel:
+//   FP32  64^2 1.43 / 1.55 / 1.97 / 2.43 / 2.69    128^2 2.09 / 1.60 / 2.11 / 2.39 / 2.73
+//         200 x 160 3.33 / 2.04 / 2.21 / 2.64 / 2.90    256^2 5.55 / 2.76 / 2.18 / 2.54 / 2.83
+//         350^2 9.26 / 4.06 / 2.77 / 3.23 / 3.54    400^2 11.6 / 4.94 / 3.97 / 3.70 / 4.18
+//   FP16  64^2 1.66 / 1.80 / 2.23 / 2.61 / 4.06    256^2 9.3 / 3.39 / 2.40 / 2.76 / 3.40
+//         350^2 16.4 / 5.43 / 3.17 / 3.56 / 4.76    400^2 20.8 / 6.59 / 4.31 / 4.16 / 4.95
+// The last tile ends where the kernels with larger tiles fill the chip
+// (16 x 16 / without): FP32 512^2 4.52 / 4.02 (one 64 x 16 tile per CU),
+// 620^2 5.98 / 7.07, 700^2 7.46 / 8.03, 800 x 700 8.26 / 8.40, 830^2 9.47 /
+// 8.58; with every state stored 640^2 8.20 / 8.67, 680^2 9.04 / 8.82; 2-byte
+// 512^2 5.24 / 5.62, 640^2 7.56 / 7.79, 700^2 8.24 / 9.60, 768^2 9.45 / 9.54,
+// 830^2 10.5 / 9.4, but 680^2 8.23 / 7.78, where the 128 x 8 tiles are just
+// under two per CU.
+template <class St, bool kChain>
+int stepk_shape(const lbm_ctx* ctx) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
+  if (tiles_total<StepKTiny>(nx, ny) <= cus) return 1;
+  if (tiles_total<StepKSmall>(nx, ny) <= 2 * cus) return 2;
+  if (tiles_total<StepKWide>(nx, ny) <= 2 * cus) return 3;
+  const int t = tiles_total<StepKLast>(nx, ny);
+  if constexpr (St::kRef) {
+    const bool two = tiles_total<StepTile<St>>(nx, ny) <= 2 * cus;
+    return 4 * t <= (two ? 25 : 36) * cus ? 4 : 0;
+  } else {
+    return !one_mid_tile_per_cu(ctx) && 2 * t <= (kChain ? 13 : 17) * cus ? 4 : 0;
+  }
+}
+
 template <bool kMid>
 void launch_step2(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
-  switch (step2_shape(ctx)) {
-    case 1: launch_step2_on<Step2Tile, kMid>(ctx, src, mid, dst); break;
-    case 2: launch_step2_on<Step2Mid, kMid>(ctx, src, mid, dst); break;
-    default: launch_step2_on<Step2Small, kMid>(ctx, src, mid, dst); break;
+  if (one_mid_tile_per_cu(ctx))
+    launch_step2_on<Step2Mid, kMid>(ctx, src, mid, dst);
+  else
+    launch_step2_on<Step2Tile, kMid>(ctx, src, mid, dst);
+}
+
+// Call fn with the tile of stepk_shape (1 .. 4).
+template <class Fn>
+void with_stepk(int shape, Fn&& fn) {
+  switch (shape) {
+    case 1: fn(StepKTiny{}); break;
+    case 2: fn(StepKSmall{}); break;
+    case 3: fn(StepKWide{}); break;
+    default: fn(StepKLast{}); break;
   }
+}
+
+// k steps from the buffer src; a single step is the step kernel's.
+template <class St, class S>
+void launch_stepk(lbm_ctx* ctx, const void* src, const StepOuts<S::K>& outs, int k, const uint16_t* ref_in,
+                  uint16_t* ref_out) {
+  if (k == 1) return launch_step<St>(ctx, src, outs.p[0], ref_in, ref_out);
+  const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
+  stepk_kernel<S, St><<<nt, S::NT, 0, ctx->stream>>>(src, outs, ref_in, ref_out, nx, ny,
+                                                     make_order(ntx, nt / ntx, ntx, false), k, ctx->c, ctx->q);
 }
 
 int check_ctx(const lbm_ctx* ctx, bool need_state) {
@@ -1784,6 +1987,26 @@ int lbm_step(lbm_ctx* ctx, int32_t n) {
   if (int st = set_device(ctx)) return st;
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
+    if (const int shape = stepk_shape<St, false>(ctx)) {
+      with_stepk(shape, [&](auto tile) {
+        using S = decltype(tile);
+        // as few launches as K steps each allow, of about equal length; for n
+        // a multiple of 4 an even number, so that a captured call ends on the
+        // buffer it started from
+        int32_t launches = n / S::K + (n % S::K != 0);
+        if (n % 4 == 0) launches += launches & 1;
+        for (int32_t left = n; launches > 0; --launches) {
+          const int a = ctx->cur, b = ctx->cur ^ 1, k = left / launches + (left % launches != 0);
+          StepOuts<S::K> outs{};
+          outs.p[k - 1] = ctx->buf[b];
+          launch_stepk<St, S>(ctx, ctx->buf[a], outs, k, ctx->ref[a], ctx->ref[b]);
+          left -= k;
+          ctx->cur = b;
+        }
+      });
+      HIP_OK(hipGetLastError());
+      return LBM_OK;
+    }
     for (int32_t s = 0; s < n;) {
       const int a = ctx->cur, b = ctx->cur ^ 1;
       if (std::is_same_v<St, StoreF32> && n - s >= 2 && use_step2(ctx)) {
@@ -1923,6 +2146,24 @@ int lbm_step_saved_chain(lbm_ctx* ctx, void* const* bufs, int32_t n) {
     if (!bufs[j] || !bufs[j + 1] || bufs[j] == bufs[j + 1])
       return fail(LBM_EINVAL, "bufs[%d] and bufs[%d] must be two distinct device buffers", j, j + 1);
   if (int st = set_device(ctx)) return st;
+  if (const int shape = stepk_shape<StoreF32, true>(ctx)) {
+    with_stepk(shape, [&](auto tile) {
+      using S = decltype(tile);
+      for (int32_t j = 0; j < n;) {
+        // up to K steps, each state a buffer the launch neither reads nor writes otherwise
+        StepOuts<S::K> outs{};
+        int k = 0;
+        for (bool fresh = true; fresh && k < S::K && j + k < n; k += fresh) {
+          for (int i = 0; i <= k; ++i) fresh = fresh && bufs[j + i] != bufs[j + k + 1];
+          if (fresh) outs.p[k] = bufs[j + k + 1];
+        }
+        launch_stepk<StoreF32, S>(ctx, bufs[j], outs, k, nullptr, nullptr);
+        j += k;
+      }
+    });
+    HIP_OK(hipGetLastError());
+    return LBM_OK;
+  }
   for (int32_t j = 0; j < n;) {
     // two steps per launch where the state two steps on goes to a third buffer
     if (n - j >= 2 && use_step2(ctx) && bufs[j + 2] != bufs[j]) {
