@@ -30,9 +30,10 @@
  *    lbm_last_error() then returns a message for the calling thread.  A
  *    failed call launches nothing and leaves the state unchanged, except
  *    LBM_EHIP (a HIP runtime error), after which the state is undefined.
- *  - The library allocates only small device scratch inside the context
- *    (reduction partials, the parameter-gradient accumulator and a status
- *    word), cleared on the stream at lbm_create; lbm_destroy frees it.
+ *  - The library allocates only small scratch inside the context (on the
+ *    device reduction partials and the parameter-gradient accumulator,
+ *    cleared on the stream at lbm_create; in pinned host memory the words
+ *    kernels return results through); lbm_destroy frees it.
  *    Every state, checkpoint and adjoint buffer belongs to the caller.
  */
 #ifndef LBM_H

@@ -308,6 +308,20 @@ __host__ __device__ __forceinline__ void equilibrium_node(T rho, T ux, T uy, con
   inverse_moments(m, f);
 }
 
+// equilibrium_node at rest (u = 0): the same bits without the terms in u.
+template <typename T>
+__host__ __device__ __forceinline__ void equilibrium_rest(T rho, const Coef<T>& c, T* f) {
+  T p, dp;
+  eos(rho, c, p, dp);
+  const T eta = T(3) * p - rho;
+  const T w0 = rho * T(1.0 / 9.0), w1 = T(2) * (eta - rho) * T(1.0 / 36.0);
+  const T w2 = (c.alpha2 * rho + c.beta2 * eta) * T(1.0 / 36.0);
+  const T A = w0 - w1 - T(2) * w2, D = w0 + T(2) * w1 + w2;
+  f[1] = f[2] = f[3] = f[4] = A;
+  f[5] = f[6] = f[7] = f[8] = D;
+  f[0] = rho - (((A + A) + (A + A)) + ((D + D) + (D + D)));
+}
+
 // Reference populations of the 2-byte storages: the rest equilibrium
 // f^eq(rho~, eta_ref(rho~), u = 0) of a reference density rho~, per velocity
 // class (0 rest, 1 axis, 2 diagonal), as cubic polynomials in rho~ whose

@@ -415,14 +415,15 @@ __device__ __forceinline__ bool interior_tile(int x0, int y0, int nx, int ny) {
 // for kBand); offsets count rows from there.  kInterior (interior_tile
 // true): every population's pull shift goes into its uniform base, so the
 // nine loads of a node share one offset register.  kWideAddr: 64-bit
-// addresses from the state's base P.p[0] (FP32, rows that wrap).
-template <class S, class St, bool kInterior = false, bool kWideAddr = false>
+// addresses from the state's base P.p[0] (FP32, rows that wrap).  kRing
+// false: the own nodes only.
+template <class S, class St, bool kInterior = false, bool kWideAddr = false, bool kRing = true>
 __device__ __forceinline__ void issue_tile(const Planes<typename St::E>& P, const uint16_t* __restrict__ rho_ref,
                                            int nx, int ny, int x0, int y0, int yb, TileRegs<S, St>& R) {
   const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * S::TX + tx;
   if constexpr (kWideAddr) {
     static_assert(sizeof(typename St::E) == 4 && !St::kRef, "64-bit addressing is for FP32 states");
-    if (tid < S::NRING) {
+    if (kRing && tid < S::NRING) {
       int hx, hy;
       ring_slot<S>(tid, hx, hy);
       pull_rows(P.p[0], wrap(x0 + hx - 1, nx), wrap(y0 + hy - 1, ny), nx, ny, R.rraw);
@@ -438,7 +439,7 @@ __device__ __forceinline__ void issue_tile(const Planes<typename St::E>& P, cons
 #pragma unroll
     for (int i = 0; i < 9; ++i) Q.p[i] = P.p[i] - (ptrdiff_t)kCy[i] * rb - kCx[i] * St::ES;
     const char* rref = reinterpret_cast<const char*>(rho_ref);  // reference plane, row pitch 2 nx bytes
-    if (tid < S::NRING) {
+    if (kRing && tid < S::NRING) {
       int hx, hy;
       ring_slot<S>(tid, hx, hy);
       const unsigned off = (unsigned)(y0 + hy - 1 - yb) * rb + (unsigned)(x0 + hx - 1) * St::ES;
@@ -460,7 +461,7 @@ __device__ __forceinline__ void issue_tile(const Planes<typename St::E>& P, cons
     asm volatile("; tile loads issued: interior" ::: "memory");
     return;
   }
-  if (tid < S::NRING) {
+  if (kRing && tid < S::NRING) {
     int hx, hy;
     ring_slot<S>(tid, hx, hy);
     const int gx = wrap(x0 + hx - 1, nx), gy = wrap(y0 + hy - 1, ny);
@@ -969,25 +970,46 @@ __device__ __forceinline__ void block_sum3(const double* in, double* red, double
 }
 
 // Moments: rho and u of main Eq. 5 plus per-workgroup FP64 partial sums of
-// mass and lattice momentum (reduced in a fixed order).
-template <class St, bool kWideAddr = false>
+// mass and lattice momentum (reduced in a fixed order; a tile's sums go to
+// the slot of its raster index).  kVel false: rho and the sums only, which
+// need neither the ring nor the force.  Bound by HBM: 48 B per node with the
+// three fields, 146 us at 4096^2 for a kernel that only moves them; loads
+// from uniform bases on interior tiles and the tile order of the step took
+// it from 194 us there and from 1636 at 16384 x 8192 (64-bit addresses on
+// every tile).
+template <class St, int kMode, bool kVel>
 __global__ __launch_bounds__(MomTile::NTHREADS) void moments_kernel(
     const void* __restrict__ src, const uint16_t* __restrict__ ref_in, float* __restrict__ rho_out,
     float* __restrict__ ux_out, float* __restrict__ uy_out, double* __restrict__ partials, int nx, int ny, int ntx,
-    Coef<float> c, RefPoly<float> q) {
+    TileOrder order, Coef<float> c, RefPoly<float> q, TileRows rows) {
   using S = MomTile;
-  __shared__ float srho[S::LDS];
+  using E = typename St::E;
+  __shared__ float srho[kVel ? S::LDS : 1];
   __shared__ double sred[3 * (S::NTHREADS / 64)];
-  const size_t N = state_layout(nx, ny, St::ES).ps;
-  const int x0 = (blockIdx.x % ntx) * S::TX, y0 = (blockIdx.x / ntx) * S::TY;
+  const Layout L = state_layout(nx, ny, St::ES);
+  int tx, tr;
+  order_tile(blockIdx.x, order, tx, tr);
+  const int ty = tile_row(rows, tr), x0 = tx * S::TX, y0 = ty * S::TY;
   float f[S::NPT][9];
   float rho[S::NPT];
   {
     TileRegs<S, St> R;
-    issue_tile<S, St, false, kWideAddr>(planes<typename St::E>(src, N), ref_in, nx, ny, x0, y0, 0, R);
-    stage_tile<S, St>(R, q, f, rho, srho, nullptr);
+    const int yb = kMode == kBand ? y0 - 2 : 0;
+    const char* sb = static_cast<const char*>(src) + (size_t)yb * St::ES * L.rp;
+    if constexpr (kMode == kWide)
+      issue_tile<S, St, false, true, kVel>(planes<E>(src, L.ps), ref_in, nx, ny, x0, y0, 0, R);
+    else if (interior_tile<S>(x0, y0, nx, ny))
+      issue_tile<S, St, true, false, kVel>(planes<E>(sb, L.ps), ref_in, nx, ny, x0, y0, yb, R);
+    else
+      issue_tile<S, St, false, false, kVel>(planes<E>(sb, L.ps), ref_in, nx, ny, x0, y0, yb, R);
+    if constexpr (kVel) {
+      stage_tile<S, St>(R, q, f, rho, srho, nullptr);
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int k = 0; k < S::NPT; ++k) decode<St>(R.raw[k], St::kRef ? R.rref[k] : 0, q, f[k]);
+    }
   }
-  __syncthreads();
   const int x = x0 + threadIdx.x;
   double sm = 0.0, sx = 0.0, sy = 0.0;
 #pragma unroll
@@ -996,41 +1018,67 @@ __global__ __launch_bounds__(MomTile::NTHREADS) void moments_kernel(
     if (x >= nx || y >= ny) continue;
     float m[9];
     forward_moments(f[k], m);
-    float nb[9], gx, gy;
-    neighbours<S>(srho, threadIdx.x + 1, ly + 1, nb);
-    stencil(nb[1], nb[2], nb[3], nb[4], nb[5], nb[6], nb[7], nb[8], gx, gy);
-    const NodeState<float> s = node_state(m[0], m[3], m[5], gx, gy, c);
     const size_t o = (size_t)y * nx + x;
     if (rho_out) rho_out[o] = m[0];
-    if (ux_out) ux_out[o] = s.ux;
-    if (uy_out) uy_out[o] = s.uy;
+    if constexpr (kVel) {
+      float nb[9], gx, gy;
+      neighbours<S>(srho, threadIdx.x + 1, ly + 1, nb);
+      stencil(nb[1], nb[2], nb[3], nb[4], nb[5], nb[6], nb[7], nb[8], gx, gy);
+      const NodeState<float> s = node_state(m[0], m[3], m[5], gx, gy, c);
+      if (ux_out) ux_out[o] = s.ux;
+      if (uy_out) uy_out[o] = s.uy;
+    }
     sm += (double)m[0];
     sx += (double)m[3];
     sy += (double)m[5];
   }
   const double v[3] = {sm, sx, sy};
-  block_sum3<S, false>(v, sred, partials, blockIdx.x);
+  block_sum3<S, false>(v, sred, partials, (unsigned)(ty * ntx + tx));
 }
 
 // Sum of the per-workgroup partials in a fixed order: each thread adds a
-// strided subset in order, then block_sum3 over the 256 threads.
+// strided subset in order, then block_sum3 over the 256 threads.  kClear:
+// the partials are zeroed once read.  One workgroup is bound by the latency
+// of its loads, so each thread keeps kAhead of them in flight (131072
+// partials took 231 us one at a time, 16384 29 us).
 constexpr int RED = 256;
 struct FlatBlock {
   static constexpr int TX = RED, NTHREADS = RED;
 };
-__global__ __launch_bounds__(RED) void finish_sums(const double* __restrict__ partials, int nblocks,
+template <bool kClear>
+__global__ __launch_bounds__(RED) void finish_sums(double* __restrict__ partials, int nblocks,
                                                    double* __restrict__ out) {
   __shared__ double red[3 * (RED / 64)];
+  constexpr int kAhead = 8;
   double a[3] = {0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < nblocks; b += RED)
-    for (int k = 0; k < 3; ++k) a[k] += partials[(size_t)b * 3 + k];
+  int b = threadIdx.x;
+  for (; b + (kAhead - 1) * RED < nblocks; b += kAhead * RED) {
+    double v[kAhead][3];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[j][k] = partials[(size_t)(b + j * RED) * 3 + k];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        a[k] += v[j][k];
+        if constexpr (kClear) partials[(size_t)(b + j * RED) * 3 + k] = 0.0;
+      }
+  }
+  for (; b < nblocks; b += RED)
+    for (int k = 0; k < 3; ++k) {
+      a[k] += partials[(size_t)b * 3 + k];
+      if constexpr (kClear) partials[(size_t)b * 3 + k] = 0.0;
+    }
   block_sum3<FlatBlock, false>(a, red, out, 0);  // one block: its slot is out[0..2]
 }
 
 // Store the post-streaming populations f of node (x, y) into the pull
-// layout: f_i goes to slot (i, x - e_i), encoded against the reference
-// density of (x, y), which is also written (2-byte storages).
-template <class St>
+// layout: f_i goes to slot (i, x - e_i), where pull_raw reads it, encoded
+// against the reference density of (x, y), which is also written (2-byte
+// storages).  kWideAddr: 64-bit addresses (states above 4 GiB).
+template <class St, bool kWideAddr, bool kStream>
 __device__ __forceinline__ void put_node(int x, int y, int nx, int ny, const float* f, const RefPoly<float>& q,
                                          void* dst, uint16_t* ref_out) {
   using E = typename St::E;
@@ -1038,77 +1086,106 @@ __device__ __forceinline__ void put_node(int x, int y, int nx, int ny, const flo
   float rd[9];
   if constexpr (St::kRef) {
     const float r = ref_density(density(f));
-    ref_out[(size_t)y * nx + x] = f32_to_f16(r);
+    *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ref_out) + 2u * ((unsigned)y * nx + (unsigned)x)) = f32_to_f16(r);
 #pragma unroll
     for (int i = 0; i < 9; ++i) rd[i] = r;
   }
-  E out[9];
-  encode<St>(f, rd, q, out);
-  E* d = reinterpret_cast<E*>(dst);
+  E o[9];
+  encode<St>(f, rd, q, o);
+  if constexpr (kWideAddr) {
+    char* const base = static_cast<char*>(dst);
+    const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+    const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    const int xs = wrap(x - kCx[i], nx), ys = wrap(y - kCy[i], ny);
-    d[(size_t)i * L.ps + (size_t)ys * L.rp + xs] = out[i];
+    for (int i = 0; i < 9; ++i) {
+      const int row = kCy[i] == 0 ? y : (kCy[i] > 0 ? ym : yp), col = kCx[i] == 0 ? x : (kCx[i] > 0 ? xm : xp);
+      put<kStream>(o[i], base + ((size_t)row * L.rp + (size_t)i * L.ps) * St::ES, St::ES * (unsigned)col);
+    }
+  } else {
+    const OutPlanes<E> Q = out_planes<E>(dst, L.ps);
+    const NodeAddr<St::ES> a = node_addr<St::ES>(x, y, nx, ny, L.rp);
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+      put<kStream>(o[i], Q.p[i],
+                   (kCy[i] == 0 ? a.r0 : (kCy[i] > 0 ? a.rm : a.rp)) + (kCx[i] == 0 ? a.c0 : (kCx[i] > 0 ? a.cm : a.cp)));
   }
 }
 
-// Initial state: f^eq(rho0, u0, eta(rho0)) at every node.  Raises *flag on a
-// density outside (0, 4/b) or a non-finite input.
+// One thread per node o of the lattice, in row order; width: make_divisor(nx).
+// These kernels move 40 (init), 72 (set, get) or 80 (adjoint seed) bytes per
+// node and are bound by HBM, with streamed stores where stream_stores says
+// so (init at 16384 x 8192: 1240 us cached, 1150 streamed; 4096^2 132 us,
+// 105 us for a kernel that only writes whole rows).
 constexpr int BLK = 256;
-template <class St>
+__device__ __forceinline__ bool flat_node(int nx, int ny, const Divisor& width, unsigned& o, int& x, int& y) {
+  o = blockIdx.x * BLK + threadIdx.x;
+  if (o >= (unsigned)nx * (unsigned)ny) return false;
+  unsigned rem;
+  y = (int)div_mod(o, width, rem);
+  x = (int)rem;
+  return true;
+}
+
+// Initial state: f^eq(rho0, u0, eta(rho0)) at every node.  Sets *flag on a
+// density outside (0, 4/b) or a non-finite input.  kRest: no velocities
+// given.
+template <class St, bool kWideAddr, bool kStream, bool kRest>
 __global__ __launch_bounds__(BLK) void init_kernel(const float* __restrict__ rho0, const float* __restrict__ ux0,
                                                    const float* __restrict__ uy0, void* __restrict__ dst,
-                                                   uint16_t* __restrict__ ref_out, int nx, int ny, Coef<float> c,
-                                                   RefPoly<float> q, int* flag) {
-  const size_t N = (size_t)nx * ny;
-  const size_t o = (size_t)blockIdx.x * BLK + threadIdx.x;
-  if (o >= N) return;
-  const float r = rho0[o], ux = ux0 ? ux0[o] : 0.0f, uy = uy0 ? uy0[o] : 0.0f;
-  if (!(r > 0.0f && c.b4 * r < 1.0f) || !isfinite(ux) || !isfinite(uy)) atomicOr(flag, 1);
+                                                   uint16_t* __restrict__ ref_out, int nx, int ny, Divisor width,
+                                                   Coef<float> c, RefPoly<float> q, int* flag) {
+  unsigned o;
+  int x, y;
+  if (!flat_node(nx, ny, width, o, x, y)) return;
+  const float r = rho0[o];
+  bool bad = !(r > 0.0f && c.b4 * r < 1.0f);
   float f[9];
-  equilibrium_node(r, ux, uy, c, f);
-  put_node<St>((int)(o % nx), (int)(o / nx), nx, ny, f, q, dst, ref_out);
+  if constexpr (kRest) {
+    equilibrium_rest(r, c, f);
+  } else {
+    const float ux = ux0 ? ux0[o] : 0.0f, uy = uy0 ? uy0[o] : 0.0f;
+    bad = bad || !isfinite(ux) || !isfinite(uy);
+    equilibrium_node(r, ux, uy, c, f);
+  }
+  if (bad) *flag = 1;  // any thread, the same value
+  put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
 }
 
 // Load a post-streaming state.
-template <class St>
+template <class St, bool kWideAddr, bool kStream>
 __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict__ fin, void* __restrict__ dst,
-                                                        uint16_t* __restrict__ ref_out, int nx, int ny,
+                                                        uint16_t* __restrict__ ref_out, int nx, int ny, Divisor width,
                                                         RefPoly<float> q) {
-  const size_t N = (size_t)nx * ny;
-  const size_t o = (size_t)blockIdx.x * BLK + threadIdx.x;
-  if (o >= N) return;
+  unsigned o;
+  int x, y;
+  if (!flat_node(nx, ny, width, o, x, y)) return;
+  const Planes<float> F = planes<float>(fin, (size_t)nx * ny);
   float f[9];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) f[i] = fin[(size_t)i * N + o];
-  put_node<St>((int)(o % nx), (int)(o / nx), nx, ny, f, q, dst, ref_out);
+  for (int i = 0; i < 9; ++i) f[i] = ldb<float>(F.p[i], 4u * o);
+  put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
 }
 
 // Export the post-streaming state f(t).
-template <class St>
+template <class St, bool kWideAddr>
 __global__ __launch_bounds__(BLK) void get_state_kernel(const void* __restrict__ src,
                                                         const uint16_t* __restrict__ ref_in, float* __restrict__ fout,
-                                                        int nx, int ny, RefPoly<float> q) {
+                                                        int nx, int ny, Divisor width, RefPoly<float> q) {
   using E = typename St::E;
-  const size_t N = (size_t)nx * ny;
-  const size_t o = (size_t)blockIdx.x * BLK + threadIdx.x;
-  if (o >= N) return;
-  const int x = (int)(o % nx), y = (int)(o / nx);
+  unsigned o;
+  int x, y;
+  if (!flat_node(nx, ny, width, o, x, y)) return;
   E raw[9];
   const Layout L = state_layout(nx, ny, St::ES);
-  if constexpr (!St::kRef) {
-    if (wide_state(nx, ny, St::ES)) {
-      pull_rows(static_cast<const char*>(src), x, y, nx, ny, raw);
-    } else {
-      pull_raw<E>(planes<E>(src, L.ps), node_addr<St::ES>(x, y, nx, ny, L.rp), raw);
-    }
-  } else {
+  if constexpr (kWideAddr)
+    pull_rows(static_cast<const char*>(src), x, y, nx, ny, raw);
+  else
     pull_raw<E>(planes<E>(src, L.ps), node_addr<St::ES>(x, y, nx, ny, L.rp), raw);
-  }
   float f[9];
   decode<St>(raw, St::kRef ? ref_in[o] : 0, q, f);
+  const OutPlanes<float> F = out_planes<float>(fout, (size_t)nx * ny);
 #pragma unroll
-  for (int i = 0; i < 9; ++i) fout[(size_t)i * N + o] = f[i];
+  for (int i = 0; i < 9; ++i) put<false>(f[i], F.p[i], 4u * o);
 }
 
 // ---------------------------------------------------------------------------
@@ -1377,17 +1454,20 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_finish_kernel(
 
 // Adjoint state (adj_layout) from a plain Lambda (planes nx*ny apart):
 // L = lam, A = 0.
+template <bool kStream>
 __global__ __launch_bounds__(BLK) void adjoint_seed_kernel(const float* __restrict__ lam, float* __restrict__ adj,
-                                                          int nx, int ny) {
-  const size_t N = (size_t)nx * ny;
-  const size_t o = (size_t)blockIdx.x * BLK + threadIdx.x;
-  if (o >= N) return;
+                                                          int nx, int ny, Divisor width) {
+  unsigned o;
+  int x, y;
+  if (!flat_node(nx, ny, width, o, x, y)) return;
   const Layout A = adj_layout(nx, ny);
-  const size_t oa = o / nx * A.rp + o % nx;
+  const Planes<float> F = planes<float>(lam, (size_t)nx * ny);
+  char* const base = reinterpret_cast<char*>(adj);
+  const unsigned oa = 4u * ((unsigned)y * A.rp + (unsigned)x);  // < 2^32 in both layouts
 #pragma unroll
-  for (int i = 0; i < 9; ++i) adj[(size_t)i * A.ps + oa] = lam[(size_t)i * N + o];
-  adj[9 * A.ps + oa] = 0.0f;
-  adj[10 * A.ps + oa] = 0.0f;
+  for (int i = 0; i < 9; ++i) put<kStream>(ldb<float>(F.p[i], 4u * o), base + (size_t)i * A.ps * 4, oa);
+  put<kStream>(0.0f, base + 9 * A.ps * 4, oa);
+  put<kStream>(0.0f, base + 10 * A.ps * 4, oa);
 }
 
 // ---------------------------------------------------------------------------
@@ -1545,6 +1625,51 @@ double* noalloc_scratch(int device) {
 
 using namespace lbm;
 
+namespace {
+// Results of a call that returns them to the host: written by the kernel
+// itself into pinned memory and read after the stream has finished.  A copy
+// to the caller's memory took another launch and a staging copy: kernel,
+// copy and wait 24 us, kernel and wait 11 us.
+struct alignas(64) HostWord {
+  double sums[3];
+  int flag;
+};
+
+// One pinned page of them for the process (allocating one per context took
+// 25-80 us of lbm_create), handed out under a lock; contexts beyond 64 get
+// an allocation of their own.
+constexpr int kHostWords = 64;
+std::mutex g_host_mu;
+HostWord* g_host_page;
+uint64_t g_host_used;
+
+hipError_t take_host_word(HostWord** out) {
+  std::lock_guard<std::mutex> lock(g_host_mu);
+  if (!g_host_page) {
+    hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g_host_page), kHostWords * sizeof(HostWord),
+                                 hipHostMallocPortable);
+    if (e != hipSuccess) {
+      g_host_page = nullptr;
+      return e;
+    }
+  }
+  if (g_host_used == ~0ull) return hipHostMalloc(reinterpret_cast<void**>(out), sizeof(HostWord), hipHostMallocPortable);
+  const int i = __builtin_ctzll(~g_host_used);
+  g_host_used |= 1ull << i;
+  *out = g_host_page + i;
+  return hipSuccess;
+}
+
+// The word's last kernel has finished.
+void give_host_word(HostWord* w) {
+  std::lock_guard<std::mutex> lock(g_host_mu);
+  if (w >= g_host_page && w < g_host_page + kHostWords)
+    g_host_used &= ~(1ull << (w - g_host_page));
+  else
+    (void)hipHostFree(w);
+}
+}  // namespace
+
 struct lbm_ctx {
   lbm_params p;
   lbm_derived d;
@@ -1560,10 +1685,11 @@ struct lbm_ctx {
   bool reverse;      // direction of the last launch with cached stores (with_stores)
   int cus;           // compute units of the device (tile-shape choice)
   int nblocks;       // workgroups of the moments tile grid
-  double* scratch;   // nblocks*3 partials, then 3 totals
-  int* flag;
+  double* scratch;   // nblocks*3 partials of the moments
   int adj_blocks;    // workgroups of the adjoint tile grid
-  double* theta;     // adj_blocks*3 accumulated partials of dL/dtheta, then 3 totals
+  double* theta;     // adj_blocks*3 accumulated partials of dL/dtheta
+  HostWord* host;    // results the kernels write for the host (pinned), and its device address
+  HostWord* host_dev;
   double* noalloc;   // the static scratch on this device (lbm_moments_noalloc), or nullptr
 };
 
@@ -1817,6 +1943,29 @@ int set_device(const lbm_ctx* ctx) {
 // the count fits a grid dimension.
 unsigned grid1(size_t n) { return static_cast<unsigned>((n + BLK - 1) / BLK); }
 
+// Call fn with v as std::bool_constant.
+template <class Fn>
+void with_bool(bool v, Fn&& fn) {
+  if (v)
+    fn(std::true_type{});
+  else
+    fn(std::false_type{});
+}
+
+// Call fn(wide, stream) for a kernel that writes (or, with stream unused,
+// reads) a whole state: 64-bit addresses for FP32 states above 4 GiB, and the
+// store policy.
+template <class St, class Fn>
+void with_state_access(const lbm_ctx* ctx, Fn&& fn) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
+  with_bool(stream_stores(9ull * St::ES * nx * ny, (unsigned long long)St::ES * nx, kCachedHbm), [&](auto stream) {
+    if constexpr (St::kRef)
+      fn(std::false_type{}, stream);
+    else
+      with_bool(wide_state(nx, ny, 4), [&](auto wide) { fn(wide, stream); });
+  });
+}
+
 // Call fn with the storage policy of the context.
 template <class Fn>
 int with_storage(const lbm_ctx* ctx, Fn&& fn) {
@@ -1885,18 +2034,19 @@ int lbm_create(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, void* r
   c->stream = (hipStream_t)stream;
   c->nblocks = tiles_total<MomTile>(p->nx, p->ny);
   c->adj_blocks = p->storage == LBM_FP32 ? tiles_total<AdjTile>(p->nx, p->ny) : 0;
-  const size_t mom_doubles = 3 * (size_t)c->nblocks + 3 + 8;  // + the status word
-  const size_t th_doubles = 3 * (size_t)c->adj_blocks + 3;
+  const size_t mom_doubles = 3 * (size_t)c->nblocks, th_doubles = 3 * (size_t)c->adj_blocks;
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess) e = hipMalloc(&c->scratch, sizeof(double) * (mom_doubles + th_doubles));
   if (e == hipSuccess) e = hipMemsetAsync(c->scratch, 0, sizeof(double) * (mom_doubles + th_doubles), c->stream);
+  if (e == hipSuccess) e = take_host_word(&c->host);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->host_dev), c->host, 0);
   if (e != hipSuccess) {
     if (c->scratch) (void)hipFree(c->scratch);
+    if (c->host) give_host_word(c->host);
     delete c;
     return fail(LBM_EHIP, "lbm_create: %s", hipGetErrorString(e));
   }
-  c->flag = reinterpret_cast<int*>(c->scratch + 3 * (size_t)c->nblocks + 3);
   c->theta = c->scratch + mom_doubles;
   c->noalloc = noalloc_scratch(c->device);  // c->device is current here
   *out = c;
@@ -1924,20 +2074,23 @@ int lbm_init(lbm_ctx* ctx, const float* rho0, const float* ux0, const float* uy0
   if (int st = check_ctx(ctx, false)) return st;
   if (!rho0) return fail(LBM_EINVAL, "rho0 is NULL");
   if (int st = set_device(ctx)) return st;
-  const size_t N = (size_t)ctx->p.nx * ctx->p.ny;
-  HIP_OK(hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream));
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
+  ctx->host->flag = 0;  // no kernel that sets it is in flight: this call waits for its own
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    init_kernel<St><<<grid1(N), BLK, 0, ctx->stream>>>(rho0, ux0, uy0, ctx->buf[0], ctx->ref[0], ctx->p.nx,
-                                                        ctx->p.ny, ctx->c, ctx->q, ctx->flag);
+    with_state_access<St>(ctx, [&](auto wide, auto stream) {
+      with_bool(!ux0 && !uy0, [&](auto rest) {
+        init_kernel<St, decltype(wide)::value, decltype(stream)::value, decltype(rest)::value>
+            <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(rho0, ux0, uy0, ctx->buf[0], ctx->ref[0], nx, ny,
+                                                             make_divisor(nx), ctx->c, ctx->q, &ctx->host_dev->flag);
+      });
+    });
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });
   if (st) return st;
-  int flag = 0;
-  HIP_OK(hipMemcpyAsync(&flag, ctx->flag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
   HIP_OK(hipStreamSynchronize(ctx->stream));
-  if (flag) {
+  if (ctx->host->flag) {
     ctx->ready = false;
     return fail(LBM_EINVAL, "rho0 must be finite and in (0, 4/b), u0 finite");
   }
@@ -1951,11 +2104,14 @@ int lbm_set_state(lbm_ctx* ctx, const float* f) {
   if (int st = check_ctx(ctx, false)) return st;
   if (!f) return fail(LBM_EINVAL, "f is NULL");
   if (int st = set_device(ctx)) return st;
-  const size_t N = (size_t)ctx->p.nx * ctx->p.ny;
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    set_state_kernel<St><<<grid1(N), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], ctx->p.nx, ctx->p.ny,
-                                                             ctx->q);
+    with_state_access<St>(ctx, [&](auto wide, auto stream) {
+      set_state_kernel<St, decltype(wide)::value, decltype(stream)::value>
+          <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], nx, ny, make_divisor(nx),
+                                                           ctx->q);
+    });
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });
@@ -1970,11 +2126,17 @@ int lbm_get_state(lbm_ctx* ctx, float* f) {
   if (int st = check_ctx(ctx, true)) return st;
   if (!f) return fail(LBM_EINVAL, "f is NULL");
   if (int st = set_device(ctx)) return st;
-  const size_t N = (size_t)ctx->p.nx * ctx->p.ny;
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
   return with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    get_state_kernel<St><<<grid1(N), BLK, 0, ctx->stream>>>(ctx->buf[ctx->cur], ctx->ref[ctx->cur], f, ctx->p.nx,
-                                                             ctx->p.ny, ctx->q);
+    auto go = [&](auto wide) {
+      get_state_kernel<St, decltype(wide)::value><<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(
+          ctx->buf[ctx->cur], ctx->ref[ctx->cur], f, nx, ny, make_divisor(nx), ctx->q);
+    };
+    if constexpr (St::kRef)
+      go(std::false_type{});
+    else
+      with_bool(wide_state(nx, ny, 4), go);
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });
@@ -2033,20 +2195,15 @@ int launch_moments(const lbm_ctx* ctx, float* rho, float* ux, float* uy, double*
   using S = MomTile;
   return with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    auto go = [&](auto wide) {
-      moments_kernel<St, decltype(wide)::value><<<tiles_total<S>(ctx->p.nx, ctx->p.ny), dim3(S::TX, S::WY), 0,
-                                                  ctx->stream>>>(ctx->buf[ctx->cur], ctx->ref[ctx->cur], rho, ux, uy,
-                                                                 partials, ctx->p.nx, ctx->p.ny,
-                                                                 tiles_x<S>(ctx->p.nx), ctx->c, ctx->q);
-    };
-    if constexpr (!St::kRef) {
-      if (wide_state(ctx->p.nx, ctx->p.ny, 4))
-        go(std::true_type{});
-      else
-        go(std::false_type{});
-    } else {
-      go(std::false_type{});
-    }
+    const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
+    with_bool(ux || uy, [&](auto vel) {
+      for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
+        moments_kernel<St, decltype(mode)::value, decltype(vel)::value>
+            <<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+                ctx->buf[ctx->cur], ctx->ref[ctx->cur], rho, ux, uy, partials, nx, ny, ntx,
+                make_order(ntx, nrows, strip_width(nx, S::TX, false), false), ctx->c, ctx->q, rows);
+      });
+    });
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });
@@ -2058,11 +2215,10 @@ int lbm_moments(lbm_ctx* ctx, float* rho, float* ux, float* uy, double totals[3]
   if (int st = set_device(ctx)) return st;
   if (int st = launch_moments(ctx, rho, ux, uy, ctx->scratch)) return st;
   if (!totals) return LBM_OK;
-  double* tot = ctx->scratch + 3 * (size_t)ctx->nblocks;
-  finish_sums<<<1, RED, 0, ctx->stream>>>(ctx->scratch, ctx->nblocks, tot);
+  finish_sums<false><<<1, RED, 0, ctx->stream>>>(ctx->scratch, ctx->nblocks, ctx->host_dev->sums);
   HIP_OK(hipGetLastError());
-  HIP_OK(hipMemcpyAsync(totals, tot, 3 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   HIP_OK(hipStreamSynchronize(ctx->stream));
+  for (int k = 0; k < 3; ++k) totals[k] = ctx->host->sums[k];
   for (int k = 0; k < 3; ++k)
     if (!std::isfinite(totals[k])) return fail(LBM_ENONFINITE, "non-finite total (%d): the state has diverged", k);
   return LBM_OK;
@@ -2080,7 +2236,7 @@ int lbm_moments_noalloc(lbm_ctx* ctx, float* rho, float* ux, float* uy, double* 
   if (int st = set_device(ctx)) return st;
   if (int st = launch_moments(ctx, rho, ux, uy, ctx->noalloc)) return st;
   if (totals_dev) {
-    finish_sums<<<1, RED, 0, ctx->stream>>>(ctx->noalloc, ctx->nblocks, totals_dev);
+    finish_sums<false><<<1, RED, 0, ctx->stream>>>(ctx->noalloc, ctx->nblocks, totals_dev);
     HIP_OK(hipGetLastError());
   }
   return LBM_OK;
@@ -2189,8 +2345,11 @@ int lbm_adjoint_seed(lbm_ctx* ctx, const float* lam, void* adj) {
   if (int st = need_fp32(ctx, "the adjoint")) return st;
   if (!lam || !adj) return fail(LBM_EINVAL, "lam and adj must be device buffers");
   if (int st = set_device(ctx)) return st;
-  const size_t N = (size_t)ctx->p.nx * ctx->p.ny;
-  adjoint_seed_kernel<<<grid1(N), BLK, 0, ctx->stream>>>(lam, static_cast<float*>(adj), ctx->p.nx, ctx->p.ny);
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
+  with_bool(stream_stores(44ull * nx * ny, 4ull * nx, kCachedHbm), [&](auto stream) {
+    adjoint_seed_kernel<decltype(stream)::value><<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(
+        lam, static_cast<float*>(adj), nx, ny, make_divisor(nx));
+  });
   HIP_OK(hipGetLastError());
   return LBM_OK;
 }
@@ -2275,18 +2434,18 @@ int lbm_adjoint_theta(lbm_ctx* ctx, double dtheta[3], int32_t reset) {
   if (int st = check_ctx(ctx, false)) return st;
   if (int st = need_fp32(ctx, "the adjoint")) return st;
   if (int st = set_device(ctx)) return st;
-  double* tot = ctx->theta + 3 * (size_t)ctx->adj_blocks;
-  if (dtheta) {
-    finish_sums<<<1, RED, 0, ctx->stream>>>(ctx->theta, ctx->adj_blocks, tot);
-    HIP_OK(hipGetLastError());
-    HIP_OK(hipMemcpyAsync(dtheta, tot, 3 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+  if (!dtheta) {
+    if (reset) HIP_OK(hipMemsetAsync(ctx->theta, 0, 3 * sizeof(double) * (size_t)ctx->adj_blocks, ctx->stream));
+    return LBM_OK;
   }
-  if (reset) HIP_OK(hipMemsetAsync(ctx->theta, 0, 3 * sizeof(double) * (size_t)ctx->adj_blocks, ctx->stream));
-  if (dtheta) {
-    HIP_OK(hipStreamSynchronize(ctx->stream));
-    for (int k = 0; k < 3; ++k)
-      if (!std::isfinite(dtheta[k])) return fail(LBM_ENONFINITE, "non-finite parameter gradient (%d)", k);
-  }
+  with_bool(reset != 0, [&](auto clear) {
+    finish_sums<decltype(clear)::value><<<1, RED, 0, ctx->stream>>>(ctx->theta, ctx->adj_blocks, ctx->host_dev->sums);
+  });
+  HIP_OK(hipGetLastError());
+  HIP_OK(hipStreamSynchronize(ctx->stream));
+  for (int k = 0; k < 3; ++k) dtheta[k] = ctx->host->sums[k];
+  for (int k = 0; k < 3; ++k)
+    if (!std::isfinite(dtheta[k])) return fail(LBM_ENONFINITE, "non-finite parameter gradient (%d)", k);
   return LBM_OK;
 }
 
@@ -2323,6 +2482,7 @@ void lbm_destroy(lbm_ctx* ctx) {
     const bool other = hipGetDevice(&cur) == hipSuccess && cur != ctx->device;
     if (other) (void)hipSetDevice(ctx->device);
     (void)hipFree(ctx->scratch);  // waits for the context's work in flight
+    if (ctx->host) give_host_word(ctx->host);
     if (other) (void)hipSetDevice(cur);
   }
   delete ctx;
