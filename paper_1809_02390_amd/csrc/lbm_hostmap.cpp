@@ -109,20 +109,31 @@ double critical_temperature(double a, double b, double r_gas) { return kCsB / kC
 int maxwell(double tr, double a, double b, double r_gas, double* rho_g, double* rho_l, double* p0) {
   const Cs cs{r_gas * tr * critical_temperature(a, b, r_gas), a, b};
   const double top = 4.0 / b;
-  // the slope is positive at small rho, negative between the spinodals and
-  // positive again near the packing limit; locate its maximum-free dip
-  const int n = 20000;
-  double s1 = -1, s2 = -1, prev = cs.slope(top * 1e-7);
-  for (int i = 1; i <= n; ++i) {
-    const double r = top * i / (n + 1.0), s = cs.slope(r);
-    if (prev > 0 && s <= 0 && s1 < 0) s1 = r;
-    if (prev <= 0 && s > 0 && s1 > 0) {
-      s2 = r;
-      break;
-    }
-    prev = s;
+  // the slope is convex in rho (its virial coefficients are positive up to
+  // the linear -2 a rho): positive at small rho, negative between the
+  // spinodals and positive again near the packing limit.  Find the first
+  // grid point of the dip and the first beyond it: a point of the dip on a
+  // coarse grid (else, for a dip narrower than that, on the fine one), then
+  // both ends by bisection of the index.
+  const int n = 20000, coarse = 100;
+  auto grid = [&](int i) { return top * i / (n + 1.0); };
+  auto dip = [&](int i) { return cs.slope(grid(i)) <= 0; };
+  int in = 0;  // a point of the dip
+  for (int i = coarse; i <= n && !in; i += coarse)
+    if (dip(i)) in = i;
+  for (int i = 1; i <= n && !in; ++i)
+    if (dip(i)) in = i;
+  if (!in || dip(n) || cs.slope(top * 1e-7) <= 0) return LBM_ENOCOEX;
+  int lo1 = 0, hi1 = in, lo2 = in, hi2 = n;  // lo1 before the dip, hi1 and lo2 in it, hi2 beyond
+  while (hi1 - lo1 > 1) {
+    const int m = (lo1 + hi1) / 2;
+    (dip(m) ? hi1 : lo1) = m;
   }
-  if (s1 < 0 || s2 < 0) return LBM_ENOCOEX;
+  while (hi2 - lo2 > 1) {
+    const int m = (lo2 + hi2) / 2;
+    (dip(m) ? lo2 : hi2) = m;
+  }
+  const double s1 = grid(hi1), s2 = grid(hi2);
   const double dr = top / (n + 1.0);
   const double r1 = bisect([&](double r) { return -cs.slope(r); }, s1 - dr, s1);  // gas spinodal
   const double r2 = bisect([&](double r) { return cs.slope(r); }, s2 - dr, s2);   // liquid spinodal
@@ -166,10 +177,8 @@ int maxwell(double tr, double a, double b, double r_gas, double* rho_g, double* 
 // thickness is int sqrt(kappa/(2 dOmega)) d rho.  The thickness integrand
 // grows like 1/(rho - rho_g) towards the ends; the logistic substitution
 // rho = rho_g + (rho_l - rho_g)/(1 + exp(-z)) makes it smooth.
-int interface_constants(double tr, double a, double b, double r_gas, double* c_sigma, double* c_w) {
-  double g, l, p0;
-  int st = maxwell(tr, a, b, r_gas, &g, &l, &p0);
-  if (st) return st;
+static int interface_integrals(double tr, double a, double b, double r_gas, double g, double l, double p0,
+                               double* c_sigma, double* c_w) {
   const Cs cs{r_gas * tr * critical_temperature(a, b, r_gas), a, b};
   const double mu0 = 0.5 * (cs.chem(g) + cs.chem(l)), kappa = 0.5 * a, d = l - g;
   auto domega = [&](double r) { return cs.free_energy(r) - mu0 * r + p0; };
@@ -186,17 +195,27 @@ int interface_constants(double tr, double a, double b, double r_gas, double* c_s
   return (std::isfinite(*c_sigma) && std::isfinite(*c_w)) ? LBM_OK : LBM_ENOCOEX;
 }
 
-int sigma_paper(double width, double tr, double a, double b, double r_gas, double* sigma) {
-  double g, l, p0, cs_, cw;
+int interface_constants(double tr, double a, double b, double r_gas, double* c_sigma, double* c_w) {
+  double g, l, p0;
   int st = maxwell(tr, a, b, r_gas, &g, &l, &p0);
-  if (st) return st;
-  st = interface_constants(tr, a, b, r_gas, &cs_, &cw);
-  if (st) return st;
+  if (!st) st = interface_integrals(tr, a, b, r_gas, g, l, p0, c_sigma, c_w);
+  return st;
+}
+
+// c^2 = 3 K_INT^2 K_EOS RT (rho Z)'(rho_l) = 1  ->  sigma = C_sigma K_INT K_EOS
+static double sigma_of(double width, double tr, double a, double b, double r_gas, double rho_l, double c_sigma,
+                       double c_w) {
   const Cs cs{r_gas * tr * critical_temperature(a, b, r_gas), a, b};
-  // c^2 = 3 K_INT^2 K_EOS RT (rho Z)'(rho_l) = 1  ->  sigma = C_sigma K_INT K_EOS
-  const double k_int = width / cw;
-  *sigma = cs_ / (3.0 * k_int * cs.repulsive_slope(l));
-  return LBM_OK;
+  const double k_int = width / c_w;
+  return c_sigma / (3.0 * k_int * cs.repulsive_slope(rho_l));
+}
+
+int sigma_paper(double width, double tr, double a, double b, double r_gas, double* sigma) {
+  double g, l, p0, c_sigma, c_w;
+  int st = maxwell(tr, a, b, r_gas, &g, &l, &p0);
+  if (!st) st = interface_integrals(tr, a, b, r_gas, g, l, p0, &c_sigma, &c_w);
+  if (!st) *sigma = sigma_of(width, tr, a, b, r_gas, l, c_sigma, c_w);
+  return st;
 }
 
 int validate(const lbm_params* p, char* msg, size_t len) {
@@ -225,13 +244,14 @@ int derive(const lbm_params* p, lbm_derived* o, char* msg, size_t len) {
   if (st) return st;
   lbm_derived d{};
   st = maxwell(p->tr, p->a, p->b, p->r_gas, &d.rho_g, &d.rho_l, &d.p0);
-  if (!st) st = interface_constants(p->tr, p->a, p->b, p->r_gas, &d.c_sigma, &d.c_w);
-  if (!st && p->sigma <= 0.0) st = sigma_paper(p->width, p->tr, p->a, p->b, p->r_gas, &d.sigma);
+  if (!st)
+    st = interface_integrals(p->tr, p->a, p->b, p->r_gas, d.rho_g, d.rho_l, d.p0, &d.c_sigma, &d.c_w);
   if (st) {
     std::snprintf(msg, len, "no two-phase coexistence found at tr = %g", p->tr);
     return st;
   }
-  if (p->sigma > 0.0) d.sigma = p->sigma;
+  d.sigma = p->sigma > 0.0 ? p->sigma
+                           : sigma_of(p->width, p->tr, p->a, p->b, p->r_gas, d.rho_l, d.c_sigma, d.c_w);
   d.width = p->width;
   d.tc = critical_temperature(p->a, p->b, p->r_gas);
   d.rt = p->r_gas * p->tr * d.tc;
@@ -262,11 +282,9 @@ int derive(const lbm_params* p, lbm_derived* o, char* msg, size_t len) {
 // taken by the fourth-order central difference of interface_constants (a
 // smooth function: fixed Gauss-Legendre panels and roots to the last bit).
 // sigma is the value the context uses (prescribed or the default rule) and
-// is held independent of W and T_r.
-int param_jacobian(const lbm_params* p, double* jac, char* msg, size_t len) {
-  lbm_derived d;
-  int st = derive(p, &d, msg, len);
-  if (st) return st;
+// is held independent of W and T_r.  d: derive() of *p.
+int param_jacobian(const lbm_params* p, const lbm_derived& d, double* jac, char* msg, size_t len) {
+  int st = LBM_OK;
   const double tr = p->tr, h = 1e-3 * std::fmin(tr, 1.0 - tr);
   double cs[4], cw[4];
   const double off[4] = {-2.0, -1.0, 1.0, 2.0};

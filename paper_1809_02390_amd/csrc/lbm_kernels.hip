@@ -2430,6 +2430,26 @@ int lbm_adjoint_init(lbm_ctx* ctx, const float* rho0, const float* ux0, const fl
   return LBM_OK;
 }
 
+namespace {
+// Queue the sum of the accumulated dL/dtheta into the context's pinned words.
+int launch_theta(const lbm_ctx* ctx, bool clear) {
+  with_bool(clear, [&](auto c) {
+    finish_sums<decltype(c)::value><<<1, RED, 0, ctx->stream>>>(ctx->theta, ctx->adj_blocks, ctx->host_dev->sums);
+  });
+  HIP_OK(hipGetLastError());
+  return LBM_OK;
+}
+
+// Wait for it.
+int wait_theta(const lbm_ctx* ctx, double dtheta[3]) {
+  HIP_OK(hipStreamSynchronize(ctx->stream));
+  for (int k = 0; k < 3; ++k) dtheta[k] = ctx->host->sums[k];
+  for (int k = 0; k < 3; ++k)
+    if (!std::isfinite(dtheta[k])) return fail(LBM_ENONFINITE, "non-finite parameter gradient (%d)", k);
+  return LBM_OK;
+}
+}  // namespace
+
 int lbm_adjoint_theta(lbm_ctx* ctx, double dtheta[3], int32_t reset) {
   if (int st = check_ctx(ctx, false)) return st;
   if (int st = need_fp32(ctx, "the adjoint")) return st;
@@ -2438,23 +2458,23 @@ int lbm_adjoint_theta(lbm_ctx* ctx, double dtheta[3], int32_t reset) {
     if (reset) HIP_OK(hipMemsetAsync(ctx->theta, 0, 3 * sizeof(double) * (size_t)ctx->adj_blocks, ctx->stream));
     return LBM_OK;
   }
-  with_bool(reset != 0, [&](auto clear) {
-    finish_sums<decltype(clear)::value><<<1, RED, 0, ctx->stream>>>(ctx->theta, ctx->adj_blocks, ctx->host_dev->sums);
-  });
-  HIP_OK(hipGetLastError());
-  HIP_OK(hipStreamSynchronize(ctx->stream));
-  for (int k = 0; k < 3; ++k) dtheta[k] = ctx->host->sums[k];
-  for (int k = 0; k < 3; ++k)
-    if (!std::isfinite(dtheta[k])) return fail(LBM_ENONFINITE, "non-finite parameter gradient (%d)", k);
-  return LBM_OK;
+  if (int st = launch_theta(ctx, reset != 0)) return st;
+  return wait_theta(ctx, dtheta);
 }
 
 int lbm_adjoint_params(lbm_ctx* ctx, double dparams[3], double dtheta[3], int32_t reset) {
   if (!dparams) return fail(LBM_EINVAL, "dparams is NULL");
-  double th[3];
-  if (int st = lbm_adjoint_theta(ctx, th, reset)) return st;
-  double jac[9];
-  if (int st = lbm::param_jacobian(&ctx->p, jac, g_err, sizeof g_err)) return st;
+  if (int st = check_ctx(ctx, false)) return st;
+  if (int st = need_fp32(ctx, "the adjoint")) return st;
+  if (int st = set_device(ctx)) return st;
+  if (int st = launch_theta(ctx, reset != 0)) return st;
+  // the parameter map's Jacobian (a few hundred us of host work) while the
+  // device finishes the sweep
+  double th[3], jac[9];
+  char msg[sizeof g_err];
+  const int bad = lbm::param_jacobian(&ctx->p, ctx->d, jac, msg, sizeof msg);
+  if (int st = wait_theta(ctx, th)) return st;
+  if (bad) return fail(bad, "%s", msg);
   for (int j = 0; j < 3; ++j) dparams[j] = jac[j] * th[0] + jac[3 + j] * th[1] + jac[6 + j] * th[2];
   if (dtheta)
     for (int k = 0; k < 3; ++k) dtheta[k] = th[k];
@@ -2463,7 +2483,9 @@ int lbm_adjoint_params(lbm_ctx* ctx, double dparams[3], double dtheta[3], int32_
 
 int lbm_param_jacobian(const lbm_params* p, double jac[9]) {
   if (!jac) return fail(LBM_EINVAL, "jac is NULL");
-  return lbm::param_jacobian(p, jac, g_err, sizeof g_err);
+  lbm_derived d;
+  if (int st = lbm::derive(p, &d, g_err, sizeof g_err)) return st;
+  return lbm::param_jacobian(p, d, jac, g_err, sizeof g_err);
 }
 
 int64_t lbm_time(const lbm_ctx* ctx) { return ctx ? ctx->t : -1; }

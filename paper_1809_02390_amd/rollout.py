@@ -91,8 +91,13 @@ class Rollout:
         self.kw = kw
         self.rec = None  # context recomputing segments on a stream of its own (backward)
         if every == "auto":
-            every = choose_every(int(nsteps), lbm_checkpoint_bytes(self.lat.params),
-                                 lbm_adjoint_bytes(self.lat.params), free_device_bytes(self.lat.f_a.device))
+            sb, ab = lbm_checkpoint_bytes(self.lat.params), lbm_adjoint_bytes(self.lat.params)
+            # what the allocator holds unused takes torch some hundred us to
+            # sum: asked only where the device's own free memory does not
+            # already hold every state
+            free, _ = torch.cuda.mem_get_info(self.lat.f_a.device)
+            every = 1 if rollout_bytes(int(nsteps), 1, sb, ab) <= 0.8 * free else choose_every(
+                int(nsteps), sb, ab, free_device_bytes(self.lat.f_a.device))
         self.nx, self.ny, self.nsteps, self.every = nx, ny, int(nsteps), int(every)
         self.starts = list(range(0, self.nsteps, self.every))
         self.ckpt = [None] * (len(self.starts) + 1)  # states at the starts, then the final state
