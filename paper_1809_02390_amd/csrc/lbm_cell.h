@@ -359,17 +359,33 @@ __host__ __device__ __forceinline__ void transpose_moments(const T* a, T* f) {
   f[8] = (D - a[8]) - (Q - P);
 }
 
+// Derivatives of the loss with respect to the per-node coefficients that
+// G'^2, K' and R T enter through.
+template <typename T>
+struct ThetaTerms {
+  T g2, erho, derho, kprt;
+};
+
+// Adds dL/d(G'^2, K', R T) of one node to a_th: kprt = K' RT,
+// e_rho = G'^2/2 - K' a, de_rho = G'^2 - 2 K' a.
+template <typename T>
+__host__ __device__ __forceinline__ void add_theta(const ThetaTerms<T>& t, const Coef<T>& c, T* a_th) {
+  a_th[0] += t.g2 + T(0.5) * t.erho + t.derho;
+  a_th[1] += c.rt * t.kprt - c.a * t.erho - T(2) * c.a * t.derho;
+  a_th[2] += c.kp * t.kprt;
+}
+
 // Reverse-mode derivative of collide_node.  Given the pre-collision
 // populations f, the stencil gradient g and lam = dL/d f-bar, returns
-// lam_f = dL/d f (at fixed g), a_g = dL/d g, and adds dL/d(G'^2, K', R T)
-// to a_th.  f-bar = f + M^T w with w from collide_scaled, so dL/dw = M lam;
+// lam_f = dL/d f (at fixed g), a_g = dL/d g, and the parameter terms (for
+// add_theta).  f-bar = f + M^T w with w from collide_scaled, so dL/dw = M lam;
 // the sweep visits the assignments of collide_scaled, node_state and eos in
 // reverse order, gathering the cotangents of the cubic velocity monomials
 // (shared by the force moments and the T and X terms) before they are
 // carried to u.
 template <typename T>
 __host__ __device__ __forceinline__ void collide_node_vjp(const T* f, T gx, T gy, const Coef<T>& c, const T* lam,
-                                                          T* lam_f, T& a_gx, T& a_gy, T* a_th) {
+                                                          T* lam_f, T& a_gx, T& a_gy, ThetaTerms<T>& th) {
   // ---- forward recomputation (collide_node) ------------------------------
   T m[9];
   forward_moments(f, m);
@@ -517,10 +533,7 @@ __host__ __device__ __forceinline__ void collide_node_vjp(const T* f, T gx, T gy
   a_rho += c.g2 * gF;
   a_gx += c.g2 * rho * a_Fx, a_gy += c.g2 * rho * a_Fy;
   a_g2 += rho * gF;
-  // parameters: kprt = K' RT, e_rho = G'^2/2 - K' a, de_rho = G'^2 - 2 K' a
-  a_th[0] += a_g2 + T(0.5) * a_erho + a_derho;
-  a_th[1] += c.rt * a_kprt - c.a * a_erho - T(2) * c.a * a_derho;
-  a_th[2] += c.kp * a_kprt;
+  th = {a_g2, a_erho, a_derho, a_kprt};
   // ---- populations: lam_f = lam + M^T dL/dm ---------------------------------
   const T am[9] = {a_rho, a_d1, a_d2, a_m3, a_d4, a_m5, a_d6, a_d7, a_d8};
   transpose_moments(am, lam_f);

@@ -370,7 +370,8 @@ inline TileOrder make_order(int ntx, int nty, int strip, bool reverse) {
 // scalar loads.  Returns the dispatch that visits the tile in the forward
 // order: one number per tile, whichever way the launch runs.
 __device__ __forceinline__ unsigned order_tile(unsigned b, const TileOrder& o, int& tx, int& ty) {
-  const unsigned xcd = b & 7, last = o.xq - (xcd < o.xr ? 0u : 1u), l = o.reverse ? last - (b >> 3) : b >> 3;
+  const unsigned xcd = b & 7, last = o.xq - (xcd < o.xr ? 0u : 1u);
+  const unsigned l = (b >> 3) + o.reverse * (last - 2u * (b >> 3));
   const unsigned t = xcd * o.xq + (xcd < o.xr ? xcd : o.xr) + l;
   unsigned rem, c;
   const unsigned s = div_mod(t, o.per, rem);
@@ -939,21 +940,54 @@ __global__ __launch_bounds__(S::NT) void stepk_kernel(const void* __restrict__ s
   }
 }
 
+// The value of the lane kOff higher (kOff a power of two) in every lane that
+// kOff does not carry across its 64, 32 or 16 lanes; elsewhere some lane's.
+// Register permutes (DPP within a row of 16 lanes, row and half swaps above)
+// instead of a trip through LDS.
+template <int kOff>
+__device__ __forceinline__ unsigned lane_up(unsigned v) {
+  if constexpr (kOff == 32) {
+    return __builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+  } else if constexpr (kOff == 16) {
+    return __builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+  } else {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + kOff, 0xF, 0xF, true);  // row_shl:kOff
+  }
+}
+template <int kOff>
+__device__ __forceinline__ double lane_up(double v) {
+  const unsigned long long b = __double_as_longlong(v);
+  const unsigned lo = lane_up<kOff>((unsigned)b), hi = lane_up<kOff>((unsigned)(b >> 32));
+  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+
+// Sum over the wave in lane 0: lane i adds lane i + 32, then + 16, ..., + 1.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += lane_up<32>(v);
+  v += lane_up<16>(v);
+  v += lane_up<8>(v);
+  v += lane_up<4>(v);
+  v += lane_up<2>(v);
+  v += lane_up<1>(v);
+  return v;
+}
+
 // Deterministic FP64 sum of three per-thread values over a block, into the
-// slot partials[3 slot .. 3 slot + 2] (added to it if kAdd, else stored):
-// a fixed shuffle tree inside each wave, then the waves' sums in wave order.
-// red holds 3 doubles per wave of LDS; it may alias LDS the block read
-// before the call.
-template <class S, bool kAdd>
+// slot partials[3 slot .. 3 slot + 2] (on top of `before`, the slot's sum so
+// far, in threads 0 .. 2): a fixed tree inside each wave, then the waves'
+// sums in wave order.  red holds 3 doubles per wave of LDS; it may alias LDS
+// the block read before the call.  The end of a workgroup waits for it, so
+// the tree stays in registers and the caller loads `before` early (adjoint
+// step of 64^2, 64 x 8 tiles: 7.33 us with the tree through LDS and the slot
+// read here, 6.79 with the slot read early, 6.61 with both).
+template <class S>
 __device__ __forceinline__ void block_sum3(const double* in, double* red, double* __restrict__ partials,
-                                           unsigned slot) {
+                                           unsigned slot, double before) {
   constexpr int NW = S::NTHREADS / 64;
   const int tid = threadIdx.y * S::TX + threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double v[3] = {in[0], in[1], in[2]};
+  double v[3];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) v[k] += __shfl_down(v[k], off, 64);
+  for (int k = 0; k < 3; ++k) v[k] = wave_sum(in[k]);
   __syncthreads();  // red may alias LDS read above
   if (lane == 0)
 #pragma unroll
@@ -962,10 +996,7 @@ __device__ __forceinline__ void block_sum3(const double* in, double* red, double
   if (tid < 3) {
     double s = red[tid * NW];
     for (int w = 1; w < NW; ++w) s += red[tid * NW + w];
-    if constexpr (kAdd)
-      partials[(size_t)slot * 3 + tid] += s;
-    else
-      partials[(size_t)slot * 3 + tid] = s;
+    partials[(size_t)slot * 3 + tid] = before + s;
   }
 }
 
@@ -1033,7 +1064,7 @@ __global__ __launch_bounds__(MomTile::NTHREADS) void moments_kernel(
     sy += (double)m[5];
   }
   const double v[3] = {sm, sx, sy};
-  block_sum3<S, false>(v, sred, partials, (unsigned)(ty * ntx + tx));
+  block_sum3<S>(v, sred, partials, (unsigned)(ty * ntx + tx), 0.0);
 }
 
 // Sum of the per-workgroup partials in a fixed order: each thread adds a
@@ -1071,7 +1102,7 @@ __global__ __launch_bounds__(RED) void finish_sums(double* __restrict__ partials
       a[k] += partials[(size_t)b * 3 + k];
       if constexpr (kClear) partials[(size_t)b * 3 + k] = 0.0;
     }
-  block_sum3<FlatBlock, false>(a, red, out, 0);  // one block: its slot is out[0..2]
+  block_sum3<FlatBlock>(a, red, out, 0, 0.0);  // one block: its slot is out[0..2]
 }
 
 // Store the post-streaming populations f of node (x, y) into the pull
@@ -1209,6 +1240,11 @@ __global__ __launch_bounds__(BLK) void get_state_kernel(const void* __restrict__
 #define LBM_ADJ_TILE 64, 8, 4
 #endif
 using AdjTile = TileShape<LBM_ADJ_TILE>;
+// Small lattices: half as wide and one node per thread.  The parameter terms
+// of the two nodes one thread of AdjTile sweeps (four rows apart) are added
+// in FP32 first here too (adjoint_tile), so the sums differ only in their
+// FP64 order.
+using AdjTileSmall = TileShape<32, 8, 8>;
 
 template <class S>
 struct AdjLds {
@@ -1307,9 +1343,9 @@ __device__ __forceinline__ void stage_nu(const float* __restrict__ ax, const flo
 // launches are reproducible bit for bit).
 template <class S>
 __device__ __forceinline__ void block_accumulate(const float* th, double* red, double* __restrict__ partials,
-                                                 unsigned slot) {
+                                                 unsigned slot, double before) {
   const double v[3] = {(double)th[0], (double)th[1], (double)th[2]};
-  block_sum3<S, true>(v, red, partials, slot);
+  block_sum3<S>(v, red, partials, slot, before);
 }
 
 // One tile of the adjoint step (kInterior: interior_tile holds, no wrap).
@@ -1365,6 +1401,7 @@ __device__ __forceinline__ void adjoint_tile(const float* __restrict__ fsrc, con
     stage_tile<S, StoreF32>(R, RefPoly<float>{}, f, rho, srho, nullptr);
   }
   put_nu<S>(h, sa, snu);  // its barriers cover srho too
+  ThetaTerms<float> own{};
   struct {
     char* p[11];
   } Q;
@@ -1382,13 +1419,31 @@ __device__ __forceinline__ void adjoint_tile(const float* __restrict__ fsrc, con
 #pragma unroll
     for (int i = 0; i < 9; ++i) lb[k][i] += snu[pos + kCy[i] * S::LW + kCx[i]];
     float lf[9], agx = 0.0f, agy = 0.0f;
-    collide_node_vjp<float>(f[k], gx, gy, c, lb[k], lf, agx, agy, th);
+    ThetaTerms<float> t;
+    collide_node_vjp<float>(f[k], gx, gy, c, lb[k], lf, agx, agy, t);
+    if constexpr (S::NPT > 1)
+      add_theta(t, c, th);
+    else
+      own = t;
     const unsigned o = o0 + (unsigned)(k * S::WY) * rb;
     // uniform field bases and one 32-bit lane offset for the eleven stores
 #pragma unroll
     for (int i = 0; i < 9; ++i) put<kStream>(lf[i], Q.p[i], o);
     put<kStream>(agx, Q.p[9], o);
     put<kStream>(agy, Q.p[10], o);
+  }
+  if constexpr (S::NPT == 1) {
+    // rows 0 .. 3 add the terms of the node four rows below to their own
+    static_assert(S::WY == 8 && AdjTile::TY == 8 && AdjTile::WY == 4, "the pairs of AdjTile");
+    static_assert(4 * sizeof(ThetaTerms<float>) / 4 * (S::NTHREADS / 2) <= 4 * AdjLds<S>::NSA, "LDS of the A halo");
+    const int tid = threadIdx.y * S::TX + threadIdx.x;
+    ThetaTerms<float>* const pair = reinterpret_cast<ThetaTerms<float>*>(sa);
+    if (tid >= S::NTHREADS / 2) pair[tid - S::NTHREADS / 2] = own;  // sa was last read ahead of put_nu's last barrier
+    __syncthreads();
+    if (tid < S::NTHREADS / 2) {
+      add_theta(own, c, th);
+      add_theta(pair[tid], c, th);
+    }
   }
 }
 
@@ -1405,6 +1460,9 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_step_kernel(const float* 
   __shared__ __align__(8) float sa[L::NSA];
   int tx, ty;
   const unsigned slot = order_tile(blockIdx.x, order, tx, ty);
+  // the slot's sum so far, loaded ahead of the sweep
+  const int tid = threadIdx.y * S::TX + threadIdx.x;
+  const double before = tid < 3 ? partials[(size_t)slot * 3 + tid] : 0.0;
   const int x0 = tx * S::TX, y0 = tile_row(rows, ty) * S::TY;
   float th[3] = {0.0f, 0.0f, 0.0f};
   if constexpr (kMode == kWide)  // the tile rows that wrap: never interior
@@ -1413,7 +1471,7 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_step_kernel(const float* 
     adjoint_tile<S, true, kMode, kStream>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
   else
     adjoint_tile<S, false, kMode, kStream>(fsrc, adj_in, adj_out, nx, ny, x0, y0, c, srho, snu, sa, th);
-  block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, slot);
+  block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, slot, before);
 }
 
 // Lambda = L + nu on the tile, then either exported (kInit false) or taken
@@ -1430,6 +1488,8 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_finish_kernel(
   const size_t N = (size_t)nx * ny;
   const Layout A = adj_layout(nx, ny);
   const int x0 = (blockIdx.x % ntx) * S::TX, y0 = (blockIdx.x / ntx) * S::TY;
+  const int tid = threadIdx.y * S::TX + threadIdx.x;
+  const double before = kInit && tid < 3 ? partials[(size_t)blockIdx.x * 3 + tid] : 0.0;
   stage_nu<S>(adj + 9 * A.ps, adj + 10 * A.ps, nx, ny, A.rp, x0, y0, sa, snu);
   float th[3] = {0.0f, 0.0f, 0.0f};
   const int x = x0 + threadIdx.x;
@@ -1449,7 +1509,7 @@ __global__ __launch_bounds__(S::NTHREADS) void adjoint_finish_kernel(
       for (int i = 0; i < 9; ++i) out[(size_t)i * N + o] = lam[i];
     }
   }
-  if constexpr (kInit) block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, blockIdx.x);
+  if constexpr (kInit) block_accumulate<S>(th, reinterpret_cast<double*>(sa), partials, blockIdx.x, before);
 }
 
 // Adjoint state (adj_layout) from a plain Lambda (planes nx*ny apart):
@@ -1926,6 +1986,14 @@ void launch_stepk(lbm_ctx* ctx, const void* src, const StepOuts<S::K>& outs, int
                                                      make_order(ntx, nt / ntx, ntx, false), k, ctx->c, ctx->q);
 }
 
+// Whether the adjoint step takes AdjTileSmall: at most three of its tiles per
+// CU.  A step is then as long as one wave's instructions, which one node per
+// thread halves: us per step, two nodes / one, 64^2 6.62 / 5.32, 256^2 7.05 /
+// 5.74, 400^2 9.96 / 8.61, but 450^2 10.3 / 10.7, 512^2 10.9 / 11.0.  A last
+// tile column of up to eight nodes costs the wider tile most: waves with so
+// few active lanes ran the sweep three times slower (70 x 64 12.8 / 5.4).
+bool small_adjoint(const lbm_ctx* ctx) { return tiles_total<AdjTileSmall>(ctx->p.nx, ctx->p.ny) <= 3 * ctx->cus; }
+
 int check_ctx(const lbm_ctx* ctx, bool need_state) {
   if (!ctx) return fail(LBM_EINVAL, "context is NULL");
   if (need_state && !ctx->ready) return fail(LBM_ESTATE, "state not initialised (call lbm_init or lbm_set_state)");
@@ -2033,10 +2101,12 @@ int lbm_create(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, void* r
   c->t = 0;
   c->stream = (hipStream_t)stream;
   c->nblocks = tiles_total<MomTile>(p->nx, p->ny);
-  c->adj_blocks = p->storage == LBM_FP32 ? tiles_total<AdjTile>(p->nx, p->ny) : 0;
-  const size_t mom_doubles = 3 * (size_t)c->nblocks, th_doubles = 3 * (size_t)c->adj_blocks;
+  
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
+  if (p->storage == LBM_FP32)
+    c->adj_blocks = small_adjoint(c) ? tiles_total<AdjTileSmall>(p->nx, p->ny) : tiles_total<AdjTile>(p->nx, p->ny);
+  const size_t mom_doubles = 3 * (size_t)c->nblocks, th_doubles = 3 * (size_t)c->adj_blocks;
   if (e == hipSuccess) e = hipMalloc(&c->scratch, sizeof(double) * (mom_doubles + th_doubles));
   if (e == hipSuccess) e = hipMemsetAsync(c->scratch, 0, sizeof(double) * (mom_doubles + th_doubles), c->stream);
   if (e == hipSuccess) e = take_host_word(&c->host);
@@ -2357,8 +2427,9 @@ int lbm_adjoint_seed(lbm_ctx* ctx, const float* lam, void* adj) {
 // One adjoint step on the context's stream (split like the forward step for
 // wide FP32 states).  Blocks of both launches add into the partial-sum
 // slots 0 .. grid-1 in launch order, so the sums stay reproducible.
-static void launch_adjoint(lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
-  using S = AdjTile;
+extern "C++" {
+template <class S>
+static void launch_adjoint_tiles(lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
   with_stores(ctx, stream_stores(44ull * nx * ny, 4ull * nx, kCachedHbm), [&](auto str, bool reverse) {
     for_tile_rows<S, true>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
@@ -2369,6 +2440,13 @@ static void launch_adjoint(lbm_ctx* ctx, const void* f_t, const void* adj_next, 
     });
   });
 }
+static void launch_adjoint(lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
+  if (small_adjoint(ctx))
+    launch_adjoint_tiles<AdjTileSmall>(ctx, f_t, adj_next, adj_out);
+  else
+    launch_adjoint_tiles<AdjTile>(ctx, f_t, adj_next, adj_out);
+}
+}  // extern "C++"
 
 int lbm_adjoint_step(lbm_ctx* ctx, const void* f_t, const void* adj_next, void* adj_out) {
   if (int st = check_ctx(ctx, false)) return st;
@@ -2409,7 +2487,7 @@ int lbm_adjoint_get(lbm_ctx* ctx, const void* adj, float* lam) {
   if (!adj || !lam) return fail(LBM_EINVAL, "adj and lam must be device buffers");
   if (int st = set_device(ctx)) return st;
   using S = AdjTile;
-  adjoint_finish_kernel<S, false><<<ctx->adj_blocks, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+  adjoint_finish_kernel<S, false><<<tiles_total<S>(ctx->p.nx, ctx->p.ny), dim3(S::TX, S::WY), 0, ctx->stream>>>(
       static_cast<const float*>(adj), lam, nullptr, nullptr, nullptr, nullptr, ctx->p.nx, ctx->p.ny,
       tiles_x<S>(ctx->p.nx), ctx->c);
   HIP_OK(hipGetLastError());
@@ -2423,7 +2501,7 @@ int lbm_adjoint_init(lbm_ctx* ctx, const float* rho0, const float* ux0, const fl
   if (!rho0 || !adj0 || !drho0) return fail(LBM_EINVAL, "rho0, adj0 and drho0 must be device buffers");
   if (int st = set_device(ctx)) return st;
   using S = AdjTile;
-  adjoint_finish_kernel<S, true><<<ctx->adj_blocks, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+  adjoint_finish_kernel<S, true><<<tiles_total<S>(ctx->p.nx, ctx->p.ny), dim3(S::TX, S::WY), 0, ctx->stream>>>(
       static_cast<const float*>(adj0), drho0, rho0, ux0, uy0, ctx->theta, ctx->p.nx, ctx->p.ny,
       tiles_x<S>(ctx->p.nx), ctx->c);
   HIP_OK(hipGetLastError());
