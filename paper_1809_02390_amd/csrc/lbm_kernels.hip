@@ -294,24 +294,28 @@ struct TileShape {
 };
 
 // Tiles of the step kernel (TX, TY, WY), per storage; compile-time tuning
-// knobs.  FP32 (bound by HBM): 256 x 8 in 1024-thread workgroups, 2-byte
-// storages (bound by the vector ALU): 128 x 8 in 512.
+// knobs.  StepTile on lattices beyond the caches (launch_step): FP32 (bound
+// by HBM) 256 x 8 in 1024-thread workgroups, 2-byte storages (bound by the
+// vector ALU) 128 x 8 in 512, two nodes per thread.  NearTile below: one node
+// per thread, so that more, shorter waves cover each other's loads.
 #ifndef LBM_STEP_TILE_F32
 #define LBM_STEP_TILE_F32 256, 8, 4
 #endif
 #ifndef LBM_STEP_TILE_16
 #define LBM_STEP_TILE_16 128, 8, 4
 #endif
+#ifndef LBM_NEAR_TILE_F32
+#define LBM_NEAR_TILE_F32 64, 4, 4
+#endif
+#ifndef LBM_NEAR_TILE_16
+#define LBM_NEAR_TILE_16 64, 8, 8
+#endif
 template <class St>
-struct StepTileOf {
-  using type = TileShape<LBM_STEP_TILE_16>;
-};
-template <>
-struct StepTileOf<StoreF32> {
-  using type = TileShape<LBM_STEP_TILE_F32>;
-};
+using StepTile =
+    std::conditional_t<St::kRef, TileShape<LBM_STEP_TILE_16>, TileShape<LBM_STEP_TILE_F32>>;
 template <class St>
-using StepTile = typename StepTileOf<St>::type;
+using NearTile =
+    std::conditional_t<St::kRef, TileShape<LBM_NEAR_TILE_16>, TileShape<LBM_NEAR_TILE_F32>>;
 using MomTile = TileShape<64, 16, 4>;
 
 // Division by a launch constant d (d >= 1): quotients of n < 2^31 from one
@@ -1816,12 +1820,12 @@ void for_tile_rows(int nx, int ny, Fn&& fn) {
 // Three ranges, measured with every size between (us per step, streamed /
 // cached; step2 is the two-step kernel, L2 4 MiB on each of 8 XCDs, memory
 // cache 256 MiB):
-//  - up to two thirds of the L2s the end of the launch, which writes them
-//    back, costs more than the next launch gains: step2 512^2 4.0 / 4.25, one
-//    step 640^2 6.2 / 7.5, FP16 1000 x 700 9.6 / 10.6; crossing over at 16 to
-//    21 MB: step2 701 x 700 8.06 / 8.04, 896^2 11.8 / 11.0, one step 701 x
-//    700 10.3 / 11.0, 768^2 12.15 / 12.03, FP16 901 x 900 12.5 / 12.6, 1024^2
-//    13.7 / 13.5;
+//  - up to half the L2s the end of the launch, which writes them back, costs
+//    more than the next launch gains (a little earlier where rows do not
+//    start on 64 bytes): one step 640^2 5.50 / 6.46, 672^2 6.07 / 6.90, 688^2
+//    8.12 / 7.04, 661 x 660 6.44 / 6.85, 666^2 7.25 / 6.95; FP16 870^2 9.0 /
+//    9.4, 910^2 11.3 / 10.2, 992^2 12.8 / 12.0; adjoint 608^2 13.8 / 15.0,
+//    624^2 17.3 / 16.5;
 //  - rows that do not start on 64 bytes share lines between workgroups, and
 //    cached stores merge them: step2 1100^2 15.9 / 14.1, 4097 x 4093 166 /
 //    159, FP16 4097 x 4093 197 / 180, adjoint 493 / 440;
@@ -1834,10 +1838,11 @@ void for_tile_rows(int nx, int ny, Fn&& fn) {
 //    to about 640 MB (step2 2048^2 42.4 / 40.7, 3000^2 91.3 / 87.3, 4096^2
 //    143.6 / 146; FP16 2048^2 48.9 / 44.9, 4000^2 164 / 158, 8192^2 627 /
 //    634).
-constexpr unsigned long long kCachedFrom = 20ull << 20, kCachedHbm = 288ull << 20, kCachedAlu = 640ull << 20;
+constexpr unsigned long long kCachedHbm = 288ull << 20, kCachedAlu = 640ull << 20;
 bool stream_stores(unsigned long long bytes, unsigned long long row, unsigned long long most) {
-  if (bytes < kCachedFrom) return true;
-  return row % 64 == 0 && 2 * bytes > most;
+  const bool aligned = row % 64 == 0;
+  if (bytes < (aligned ? 16ull : 15ull) << 20) return true;
+  return aligned && 2 * bytes > most;
 }
 
 // Call fn(stream, reverse) for one launch (or the launches of one step):
@@ -1853,10 +1858,9 @@ void with_stores(lbm_ctx* ctx, bool stream, Fn&& fn) {
 // One step of storage St with tile shape S from the buffer src (and its
 // reference plane) to dst, on the context's stream.
 template <class St, class S>
-void launch_step_tiles(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
+void launch_step_tiles(lbm_ctx* ctx, bool stream, const void* src, void* dst, const uint16_t* ref_in,
+                       uint16_t* ref_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
-  const bool stream = stream_stores((9ull * St::ES + (St::kRef ? 2 : 0)) * nx * ny, (unsigned long long)St::ES * nx,
-                                    St::kRef ? kCachedAlu : kCachedHbm);
   with_stores(ctx, stream, [&](auto str, bool reverse) {
     for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
       step_kernel<S, St, decltype(mode)::value, decltype(str)::value>
@@ -1867,22 +1871,24 @@ void launch_step_tiles(lbm_ctx* ctx, const void* src, void* dst, const uint16_t*
   });
 }
 
-// Smaller tiles for small lattices: the storage's own tile while it gives at
-// least one tile per CU, then 128 x 8 (FP32), then 64 x 4.  Measured, FP32
-// step: 256^2 6.0 / 4.8 / 3.6 us (256 x 8 / 128 x 8 / 64 x 4), 512^2 7.4 /
-// 5.9 / 6.1 us, 1024^2 19.4 / 20.2 / 21.0 us.  The per-node arithmetic does
-// not depend on the tile, so every choice gives the same bits.
-using SmallTile = TileShape<64, 4, 4>;
-using MidTileF32 = TileShape<128, 8, 4>;
-
+// One step: NearTile while the caches hold source and destination (as far as
+// the storage's kernel gains from them, stream_stores), StepTile beyond.
+// Measured, us per step, NearTile / StepTile (FP32 on small lattices: 128 x
+// 8): FP32 512^2 4.72 / 5.05, 560^2 5.00 / 6.33, 1000 x 700 9.4 / 12.4, 2085
+// x 1035 25.5 / 30.2, 2048^2 69 / 59, 4096^2 257 / 197; FP16 1000 x 700 8.36
+// / 9.79, 1024^2 12.4 / 14.0, 2048^2 39.8 / 42.8, 4096^2 161.9 / 161.5,
+// 8192^2 634 / 618.  The per-node arithmetic does not depend on the tile, so
+// both give the same bits.
 template <class St>
 void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
-  if (tiles_total<StepTile<St>>(nx, ny) >= ctx->cus) return launch_step_tiles<St, StepTile<St>>(ctx, src, dst, ref_in, ref_out);
-  if constexpr (std::is_same_v<St, StoreF32>)
-    if (tiles_total<MidTileF32>(nx, ny) >= ctx->cus)
-      return launch_step_tiles<St, MidTileF32>(ctx, src, dst, ref_in, ref_out);
-  launch_step_tiles<St, SmallTile>(ctx, src, dst, ref_in, ref_out);
+  const unsigned long long bytes = (9ull * St::ES + (St::kRef ? 2 : 0)) * nx * ny;
+  const unsigned long long most = St::kRef ? kCachedAlu : kCachedHbm;
+  const bool stream = stream_stores(bytes, (unsigned long long)St::ES * nx, most);
+  if (2 * bytes <= most)
+    launch_step_tiles<St, NearTile<St>>(ctx, stream, src, dst, ref_in, ref_out);
+  else
+    launch_step_tiles<St, StepTile<St>>(ctx, stream, src, dst, ref_in, ref_out);
 }
 
 // Two FP32 steps per launch (step2_kernel), on lattices too large for
@@ -1933,15 +1939,14 @@ bool one_mid_tile_per_cu(const lbm_ctx* ctx) {
 //   FP32  64^2 1.43 / 1.55 / 1.97 / 2.43 / 2.69    128^2 2.09 / 1.60 / 2.11 / 2.39 / 2.73
 //         200 x 160 3.33 / 2.04 / 2.21 / 2.64 / 2.90    256^2 5.55 / 2.76 / 2.18 / 2.54 / 2.83
 //         350^2 9.26 / 4.06 / 2.77 / 3.23 / 3.54    400^2 11.6 / 4.94 / 3.97 / 3.70 / 4.18
-//   FP16  64^2 1.66 / 1.80 / 2.23 / 2.61 / 4.06    256^2 9.3 / 3.39 / 2.40 / 2.76 / 3.40
-//         350^2 16.4 / 5.43 / 3.17 / 3.56 / 4.76    400^2 20.8 / 6.59 / 4.31 / 4.16 / 4.95
+//   FP16  64^2 1.66 / 1.80 / 2.23 / 2.61 / 4.06    256^2 9.3 / 3.39 / 2.40 / 2.76 / 3.59
+//         350^2 16.4 / 5.43 / 3.17 / 3.56 / 4.86    400^2 20.8 / 6.59 / 4.31 / 4.16 / 5.08
 // The last tile ends where the kernels with larger tiles fill the chip
 // (16 x 16 / without): FP32 512^2 4.52 / 4.02 (one 64 x 16 tile per CU),
 // 620^2 5.98 / 7.07, 700^2 7.46 / 8.03, 800 x 700 8.26 / 8.40, 830^2 9.47 /
 // 8.58; with every state stored 640^2 8.20 / 8.67, 680^2 9.04 / 8.82; 2-byte
-// 512^2 5.24 / 5.62, 640^2 7.56 / 7.79, 700^2 8.24 / 9.60, 768^2 9.45 / 9.54,
-// 830^2 10.5 / 9.4, but 680^2 8.23 / 7.78, where the 128 x 8 tiles are just
-// under two per CU.
+// 500^2 5.06 / 5.28, 560^2 5.97 / 6.23, 600^2 6.57 / 6.27, 640^2 7.56 / 6.92,
+// 700^2 8.26 / 6.95.
 template <class St, bool kChain>
 int stepk_shape(const lbm_ctx* ctx) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
@@ -1950,8 +1955,7 @@ int stepk_shape(const lbm_ctx* ctx) {
   if (tiles_total<StepKWide>(nx, ny) <= 2 * cus) return 3;
   const int t = tiles_total<StepKLast>(nx, ny);
   if constexpr (St::kRef) {
-    const bool two = tiles_total<StepTile<St>>(nx, ny) <= 2 * cus;
-    return 4 * t <= (two ? 25 : 36) * cus ? 4 : 0;
+    return 2 * t <= 11 * cus ? 4 : 0;
   } else {
     return !one_mid_tile_per_cu(ctx) && 2 * t <= (kChain ? 13 : 17) * cus ? 4 : 0;
   }
