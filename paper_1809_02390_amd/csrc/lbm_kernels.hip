@@ -1892,8 +1892,7 @@ void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_i
 }
 
 // Two FP32 steps per launch (step2_kernel), on lattices too large for
-// stepk_kernel: tiles of 64 x 24, or of 64 x 16 where those come to one per
-// CU (512^2, us per step: 4.02 against 4.52 for stepk_kernel).  The tiles
+// stepk_kernel: tiles of 64 x 24 or of 64 x 16 (mid_tile_first).  The tiles
 // address TY + 8 rows of 36 nx bytes from one base with 32-bit offsets,
 // which bounds the width (about 3.7M nodes); wider lattices take single
 // steps.
@@ -1925,7 +1924,8 @@ using StepKWide = TileKShape<32, 8, 3>;
 using StepKLast = TileKShape<16, 16, 2>;
 
 // Whether a lattice has just enough 64 x 16 tiles for the two-step kernel to
-// run one per CU (7/8 of the CUs to all of them).
+// run one per CU (7/8 of the CUs to all of them), where it beats stepk_kernel
+// (512^2, us per step: 4.02 against 4.52).
 bool one_mid_tile_per_cu(const lbm_ctx* ctx) {
   const int t = tiles_total<Step2Mid>(ctx->p.nx, ctx->p.ny);
   return t <= ctx->cus && 8 * t > 7 * ctx->cus;
@@ -1961,9 +1961,23 @@ int stepk_shape(const lbm_ctx* ctx) {
   }
 }
 
+// Whether the 64 x 16 tile finishes the lattice first: the CUs work through
+// ceil(tiles / CUs) workgroups each, and one of its takes 0.73 of the time of
+// one of 64 x 24.  Where the larger tile leaves its last turn nearly empty
+// the smaller one wins (us per step, 64 x 24 / 64 x 16, workgroups per CU in
+// brackets): 830^2 8.5 / 8.7 (1.8 / 2.6), 900^2 11.0 / 10.4 (2.2 / 3.3), 1024^2
+// 11.9 / 11.5 (2.7 / 4), 1100^2 14.1 / 13.5 (3.2 / 4.9), 1200^2 14.9 / 15.4
+// (3.7 / 5.6), 1500^2 21.5 / 23.3 (5.9 / 8.8).
+bool mid_tile_first(const lbm_ctx* ctx) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
+  const long long large = (tiles_total<Step2Tile>(nx, ny) + cus - 1) / cus;
+  const long long mid = (tiles_total<Step2Mid>(nx, ny) + cus - 1) / cus;
+  return 73 * mid < 100 * large;
+}
+
 template <bool kMid>
 void launch_step2(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
-  if (one_mid_tile_per_cu(ctx))
+  if (mid_tile_first(ctx))
     launch_step2_on<Step2Mid, kMid>(ctx, src, mid, dst);
   else
     launch_step2_on<Step2Tile, kMid>(ctx, src, mid, dst);

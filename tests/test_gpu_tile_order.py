@@ -19,8 +19,9 @@ def _field(nx, ny, seed):
 
 
 # 800 x 801: rows on 64 bytes; 2600 x 257: strips of tiles with a narrower
-# last one; 769 x 903: rows off 64 bytes.  One-step states of 20 MiB and more.
-@pytest.mark.parametrize("nx,ny", [(800, 801), (2600, 257), (769, 903)])
+# last one; 769 x 903: rows off 64 bytes; 900 x 905: two steps on 64 x 16
+# tiles, the others on 64 x 24.  One-step states of 20 MiB and more.
+@pytest.mark.parametrize("nx,ny", [(800, 801), (2600, 257), (769, 903), (900, 905)])
 def test_launch_directions_agree_fp32(nx, ny):
     """Two launches in a row from the same buffers run in opposite
     directions: one-step kernel, adjoint kernel and its parameter sums
