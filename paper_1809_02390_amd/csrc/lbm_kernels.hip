@@ -1109,6 +1109,21 @@ __global__ __launch_bounds__(RED) void finish_sums(double* __restrict__ partials
   block_sum3<FlatBlock>(a, red, out, 0, 0.0);  // one block: its slot is out[0..2]
 }
 
+// Halo coordinates (hx, hy) of the entries p = tid, tid + NTHREADS, ... of
+// a W-wide row-major table, stepped without divisions: one division for the
+// first entry, then NTHREADS = DY W + DX per step.
+template <int W, int NTHREADS>
+struct HaloWalk {
+  static constexpr int DY = NTHREADS / W, DX = NTHREADS % W;
+  int hx, hy;
+  __device__ __forceinline__ explicit HaloWalk(int p) : hx(p % W), hy(p / W) {}
+  __device__ __forceinline__ void next() {
+    hx += DX;
+    hy += DY;
+    if (hx >= W) hx -= W, ++hy;
+  }
+};
+
 // Store the post-streaming populations f of node (x, y) into the pull
 // layout: f_i goes to slot (i, x - e_i), where pull_raw reads it, encoded
 // against the reference density of (x, y), which is also written (2-byte
@@ -1149,8 +1164,7 @@ __device__ __forceinline__ void put_node(int x, int y, int nx, int ny, const flo
 // One thread per node o of the lattice, in row order; width: make_divisor(nx).
 // These kernels move 40 (init), 72 (set, get) or 80 (adjoint seed) bytes per
 // node and are bound by HBM, with streamed stores where stream_stores says
-// so (init at 16384 x 8192: 1240 us cached, 1150 streamed; 4096^2 132 us,
-// 105 us for a kernel that only writes whole rows).
+// so.
 constexpr int BLK = 256;
 __device__ __forceinline__ bool flat_node(int nx, int ny, const Divisor& width, unsigned& o, int& x, int& y) {
   o = blockIdx.x * BLK + threadIdx.x;
@@ -1186,7 +1200,88 @@ __global__ __launch_bounds__(BLK) void init_kernel(const float* __restrict__ rho
   put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
 }
 
-// Load a post-streaming state.
+// The initial state at rest of lattices that stream past the caches
+// (launch_init), by tiles: the three class values of every node of the tile
+// and its ring go to LDS, and each slot of the pull layout takes its own from
+// there, so that whole aligned rows are stored.  One node per thread
+// (init_kernel) stores rows shifted by the streaming, whose ends share lines
+// with the next workgroup's: FP32 4096^2 152 us against 97, 8192^2 627 / 366,
+// 16384 x 8192 1115 / 906 (tiles of 256 x 8 in 512 threads; 64 x 16: 100, 400,
+// 1147), FP16 4096^2 98 / 58, 16384 x 8192 754 / 696 (64 x 16; 256 x 8: 65,
+// 705).  On lattices the caches hold it gains nothing.
+template <int TX_, int TY_, int WY_>
+struct InitShape {
+  static constexpr int TX = TX_, TY = TY_, WY = WY_, NPT = TY / WY, LW = TX + 2;
+  static constexpr int NTHREADS = TX * WY, LDS = (TY + 2) * LW;
+};
+template <class St>
+using InitTile = std::conditional_t<St::kRef, InitShape<64, 16, 4>, InitShape<256, 8, 2>>;
+
+template <class St>
+__global__ __launch_bounds__(InitTile<St>::NTHREADS) void init_rest_kernel(const float* __restrict__ rho0,
+                                                                      void* __restrict__ dst,
+                                                                      uint16_t* __restrict__ ref_out, int nx, int ny,
+                                                                      TileOrder order, Coef<float> c,
+                                                                      RefPoly<float> q, int* flag) {
+  using S = InitTile<St>;
+  using E = typename St::E;
+  __shared__ E sv[3 * S::LDS];
+  int tx, ty;
+  order_tile(blockIdx.x, order, tx, ty);
+  const int x0 = tx * S::TX, y0 = ty * S::TY, tid = threadIdx.y * S::TX + threadIdx.x;
+  constexpr int kRounds = (S::LDS + S::NTHREADS - 1) / S::NTHREADS;
+  float r[kRounds];
+  {
+    HaloWalk<S::LW, S::NTHREADS> w(tid);
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k, w.next())
+      if (tid + k * S::NTHREADS < S::LDS)
+        r[k] = ldb<float>(reinterpret_cast<const char*>(rho0),
+                          4u * ((unsigned)wrap(y0 + w.hy - 1, ny) * (unsigned)nx + (unsigned)wrap(x0 + w.hx - 1, nx)));
+  }
+  HaloWalk<S::LW, S::NTHREADS> w(tid);
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < kRounds; ++k, w.next()) {
+    const int p = tid + k * S::NTHREADS;
+    if (p >= S::LDS) break;
+    bad = bad || !(r[k] > 0.0f && c.b4 * r[k] < 1.0f);
+    float f[9];
+    equilibrium_rest(r[k], c, f);
+    E o[9];
+    float rd[9];
+    if constexpr (St::kRef) {
+      const float rt = ref_density(density(f));
+#pragma unroll
+      for (int i = 0; i < 9; ++i) rd[i] = rt;
+      const int x = x0 + w.hx - 1, y = y0 + w.hy - 1;
+      if (w.hx >= 1 && w.hx <= S::TX && w.hy >= 1 && w.hy <= S::TY && x < nx && y < ny)
+        *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ref_out) + 2u * ((unsigned)y * nx + (unsigned)x)) =
+            f32_to_f16(rt);
+    }
+    encode<St>(f, rd, q, o);
+    sv[p] = o[0], sv[S::LDS + p] = o[1], sv[2 * S::LDS + p] = o[5];
+  }
+  if (bad) *flag = 1;  // any thread, the same value
+  __syncthreads();
+  const int x = x0 + threadIdx.x;
+  if (x >= nx) return;
+  const Layout L = state_layout(nx, ny, St::ES);
+  char* const base = static_cast<char*>(dst) + (size_t)y0 * L.rp * St::ES;
+#pragma unroll
+  for (int k = 0; k < S::NPT; ++k) {
+    const int ly = threadIdx.y + k * S::WY;
+    if (y0 + ly >= ny) break;
+    const unsigned off = St::ES * ((unsigned)ly * L.rp + (unsigned)x);  // rows of the tile: below 2^32 (launch_init)
+    const int pos = (ly + 1) * S::LW + threadIdx.x + 1;
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+      put<true>(sv[velocity_class(i) * S::LDS + pos + kCy[i] * S::LW + kCx[i]], base + (size_t)i * L.ps * St::ES, off);
+  }
+}
+
+// Load a post-streaming state (FP32 with the shift in the loads, us against
+// in the stores: 512^2 3.6 / 4.3, 4096^2 199 / 233, 16384 x 8192 1608 / 1805).
 template <class St, bool kWideAddr, bool kStream>
 __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict__ fin, void* __restrict__ dst,
                                                         uint16_t* __restrict__ ref_out, int nx, int ny, Divisor width,
@@ -1195,10 +1290,24 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
   int x, y;
   if (!flat_node(nx, ny, width, o, x, y)) return;
   const Planes<float> F = planes<float>(fin, (size_t)nx * ny);
-  float f[9];
+  if constexpr (!St::kRef) {
+    // a permutation: slot (i, x) is f_i of node x + e_i.  The shift goes into
+    // the loads, so that whole rows are stored.
+    const Layout L = state_layout(nx, ny, 4);
+    const NodeAddr<4> a = node_addr<4>(x, y, nx, ny, (unsigned)nx);
+    char* const base = static_cast<char*>(dst) + (kWideAddr ? (size_t)y * L.rp * 4 : 0);
+    const unsigned off = 4u * ((kWideAddr ? 0u : (unsigned)y * L.rp) + (unsigned)x);
 #pragma unroll
-  for (int i = 0; i < 9; ++i) f[i] = ldb<float>(F.p[i], 4u * o);
-  put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
+    for (int i = 0; i < 9; ++i) {
+      const unsigned from = (kCy[i] == 0 ? a.r0 : (kCy[i] > 0 ? a.rp : a.rm)) + (kCx[i] == 0 ? a.c0 : (kCx[i] > 0 ? a.cp : a.cm));
+      put<kStream>(ldb<float>(F.p[i], from), base + (size_t)i * L.ps * 4, off);
+    }
+  } else {
+    float f[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) f[i] = ldb<float>(F.p[i], 4u * o);
+    put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
+  }
 }
 
 // Export the post-streaming state f(t).
@@ -1264,21 +1373,6 @@ template <class S>
 struct AHalo {
   static constexpr int R = (AdjLds<S>::NA + S::NTHREADS - 1) / S::NTHREADS;
   float v[R][2];
-};
-
-// Halo coordinates (hx, hy) of the entries p = tid, tid + NTHREADS, ... of
-// a W-wide row-major table, stepped without divisions: one division for the
-// first entry, then NTHREADS = DY W + DX per step.
-template <int W, int NTHREADS>
-struct HaloWalk {
-  static constexpr int DY = NTHREADS / W, DX = NTHREADS % W;
-  int hx, hy;
-  __device__ __forceinline__ explicit HaloWalk(int p) : hx(p % W), hy(p / W) {}
-  __device__ __forceinline__ void next() {
-    hx += DX;
-    hy += DY;
-    if (hx >= W) hx -= W, ++hy;
-  }
 };
 
 // 32-bit byte offsets from the A planes' bases: (y rp + x) 4 < 44 nx ny for
@@ -2052,6 +2146,32 @@ void with_state_access(const lbm_ctx* ctx, Fn&& fn) {
   });
 }
 
+// Queue the initial state (init_rest_kernel where it streams, at rest, and
+// its tiles' rows fit 32-bit offsets; else init_kernel).
+template <class St>
+void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const float* uy0) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
+  const bool rest = !ux0 && !uy0;
+  int* const flag = &ctx->host_dev->flag;
+  with_state_access<St>(ctx, [&](auto wide, auto stream) {
+    using S = InitTile<St>;
+    const unsigned long long row = 9ull * St::ES * nx;
+    if constexpr (decltype(stream)::value)
+      if (rest && row * ny >= 16ull << 20 && row * S::TY < 1ull << 32) {
+        const int ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
+        init_rest_kernel<St><<<nt, dim3(S::TX, S::WY), 0, ctx->stream>>>(
+            rho0, ctx->buf[0], ctx->ref[0], nx, ny, make_order(ntx, nt / ntx, strip_width(nx, S::TX, false), false),
+            ctx->c, ctx->q, flag);
+        return;
+      }
+    with_bool(rest, [&](auto r) {
+      init_kernel<St, decltype(wide)::value, decltype(stream)::value, decltype(r)::value>
+          <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(rho0, ux0, uy0, ctx->buf[0], ctx->ref[0], nx, ny,
+                                                           make_divisor(nx), ctx->c, ctx->q, flag);
+    });
+  });
+}
+
 // Call fn with the storage policy of the context.
 template <class Fn>
 int with_storage(const lbm_ctx* ctx, Fn&& fn) {
@@ -2162,17 +2282,9 @@ int lbm_init(lbm_ctx* ctx, const float* rho0, const float* ux0, const float* uy0
   if (int st = check_ctx(ctx, false)) return st;
   if (!rho0) return fail(LBM_EINVAL, "rho0 is NULL");
   if (int st = set_device(ctx)) return st;
-  const int nx = ctx->p.nx, ny = ctx->p.ny;
   ctx->host->flag = 0;  // no kernel that sets it is in flight: this call waits for its own
   int st = with_storage(ctx, [&](auto store) -> int {
-    using St = decltype(store);
-    with_state_access<St>(ctx, [&](auto wide, auto stream) {
-      with_bool(!ux0 && !uy0, [&](auto rest) {
-        init_kernel<St, decltype(wide)::value, decltype(stream)::value, decltype(rest)::value>
-            <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(rho0, ux0, uy0, ctx->buf[0], ctx->ref[0], nx, ny,
-                                                             make_divisor(nx), ctx->c, ctx->q, &ctx->host_dev->flag);
-      });
-    });
+    launch_init<decltype(store)>(ctx, rho0, ux0, uy0);
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });

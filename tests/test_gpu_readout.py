@@ -55,6 +55,38 @@ def test_initial_state_matches_oracle(vel):
     lat.close()
 
 
+@pytest.mark.parametrize("nx,ny,storage", [(2560, 1603, "fp32"), (4096, 2117, "fp16"), (4096, 2117, "bf16")])
+def test_initial_state_by_tiles(nx, ny, storage):
+    """Lattices that stream past the caches, partial last tile rows: the
+    state at rest, stored by tiles, is that of zero velocities, stored node
+    by node, bit for bit; and a bad density is seen."""
+    _, rho, _, lat = _lat(nx, ny, storage)
+    rho = torch.as_tensor(rho, dtype=torch.float32, device="cuda")
+    zero = torch.zeros((ny, nx), device="cuda")
+    rest = lat.init(rho).save_state()
+    moving = lat.init(rho, zero, zero).save_state()
+    used = 9 * nx * ny * (4 if storage == "fp32" else 2)
+    assert torch.equal(rest[:used], moving[:used])
+    if storage != "fp32":
+        assert torch.equal(rest[-2 * nx * ny:], moving[-2 * nx * ny:])
+    for at in ((0, 0), (ny - 1, nx - 1)):
+        bad = rho.clone()
+        bad[at] = float("nan")
+        with pytest.raises(pkg.LbmError):
+            lat.init(bad)
+    lat.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (3, 2), (70, 37), (512, 512), (2085, 1035), (2560, 1603)])
+def test_loaded_state_is_exported_unchanged(nx, ny):
+    """lbm_set_state and lbm_get_state of FP32 states: a permutation and its
+    inverse, bit for bit."""
+    f = torch.randn((9, ny, nx), generator=torch.Generator(device="cuda").manual_seed(nx), device="cuda")
+    lat = pkg.Lattice(nx, ny, tr=0.7).set_state(f)
+    assert torch.equal(lat.state(), f)
+    lat.close()
+
+
 def test_refused_densities_leave_no_state():
     """A density outside (0, 4/b) or not finite is refused, and a later good
     field is accepted."""
