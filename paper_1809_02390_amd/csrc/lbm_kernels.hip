@@ -1965,20 +1965,20 @@ void launch_step_tiles(lbm_ctx* ctx, bool stream, const void* src, void* dst, co
   });
 }
 
-// One step: NearTile while the memory cache holds source and destination,
-// StepTile beyond.  Measured, us per step, NearTile / StepTile (FP32 on small
-// lattices: 128 x 8): FP32 512^2 4.72 / 5.05, 560^2 5.00 / 6.33, 1000 x 700
-// 9.4 / 12.4, 2085 x 1035 25.5 / 30.2, 2048^2 69 / 59, 4096^2 257 / 197; FP16
-// 1000 x 700 8.36 / 9.79, 1024^2 12.4 / 14.0, 2048^2 38.7 / 45.0, 2560^2 64.8
-// / 66.0, 3072^2 103.9 / 99.2, 4096^2 167.1 / 162.7, 8192^2 634 / 618.  The
-// per-node arithmetic does not depend on the tile, so both give the same
-// bits.
+// One step: NearTile while the 256 MiB memory cache holds source and
+// destination, StepTile beyond.  Measured, us per step, NearTile / StepTile
+// (FP32 on small lattices: 128 x 8): FP32 512^2 4.72 / 5.05, 560^2 5.00 /
+// 6.33, 1000 x 700 9.4 / 12.4, 2085 x 1035 25.5 / 30.2, 1900^2 39.1 / 44.7,
+// 1984^2 59.7 / 57.6, 2048^2 68.1 / 57.8, 4096^2 257 / 197; FP16 1000 x 700
+// 8.36 / 9.79, 1024^2 12.4 / 14.0, 2048^2 38.7 / 45.0, 2560^2 64.8 / 66.0,
+// 3072^2 103.9 / 99.2, 4096^2 167.1 / 162.7, 8192^2 634 / 618.  The per-node
+// arithmetic does not depend on the tile, so both give the same bits.
 template <class St>
 void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_in, uint16_t* ref_out) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   const unsigned long long bytes = (9ull * St::ES + (St::kRef ? 2 : 0)) * nx * ny;
   const bool stream = stream_stores(bytes, (unsigned long long)St::ES * nx, St::kRef ? kCachedAlu : kCachedHbm);
-  if (2 * bytes <= kCachedHbm)
+  if (2 * bytes <= 256ull << 20)
     launch_step_tiles<St, NearTile<St>>(ctx, stream, src, dst, ref_in, ref_out);
   else
     launch_step_tiles<St, StepTile<St>>(ctx, stream, src, dst, ref_in, ref_out);
