@@ -796,6 +796,160 @@ __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restr
 }
 
 // ---------------------------------------------------------------------------
+// Two time steps per launch on large lattices (FP32 storage), marching: a
+// workgroup walks down a strip of kMarchCols columns, one thread per column
+// of the strip and its halo and one row per iteration, with both steps as a
+// pipeline of rows behind the row being loaded.  Iteration m (rows counted
+// from the first of the workgroup's segment)
+//   (B) collides row m - 5 of step t, whose stencil reads the densities of
+//       rows m - 6 .. m - 4, and pushes its populations to the rows they
+//       stream to;
+//   (A) stages the densities of row m - 3, which the iteration before
+//       loaded, and issues the loads of row m - 2;
+//   (D) collides row m - 9 of step t + 1 and stores it;
+//   (C) takes back the nine populations that have arrived at row m - 7 and
+//       stages its densities.
+// A phase reads only what earlier iterations left in LDS, so an iteration
+// has one barrier.  The rows in flight are held in rings of four slots (two
+// for populations that move up, which are read one iteration after their
+// write), indexed by constants: the loop is unrolled four times.  Every node
+// is updated by the operations of step_kernel in the same order.
+//
+// What bounds it: the vector ALU, as in step2_kernel, but without that
+// kernel's halo of a 64 x 24 tile (12 % more collisions), its side nodes,
+// row tests and addresses: 460 instructions per thread and iteration, the
+// arithmetic of two updates, against 283 per update.  An iteration of 16
+// waves takes 3.35 us, 97 % of what the ALU allows.  One workgroup of 1024
+// threads per CU: its barrier keeps the waves of a SIMD together, where four
+// workgroups of 256 drift apart and leave it to the slowest at the end
+// (4096^2: 147 us per step), and its strip has the fewest partial lines.
+// The 32 columns left of the strip put the first thread's loads and the
+// stores on 128-byte lines (8192^2: 495 us; with 16 columns more of the 1024
+// threads stored, 503).  A segment costs about eight rows more than it
+// has: the pipeline fills (16 us for the first eight iterations) and drains.
+// Measured, us per step, step2_kernel / this: 3072^2 87.7 / 86.3, 5000 x 3000
+// 143 / 132, 4096^2 144.2 / 137.4, 4097 x 4093 156 / 146, 6000 x 5000 267 / 240,
+// 8192^2 543 / 499, 16384 x 8192 1107 / 1016.
+// ---------------------------------------------------------------------------
+constexpr int kMarchThreads = 1024, kMarchLeft = 32, kMarchCols = 960;
+static_assert(kMarchLeft + kMarchCols + 3 <= kMarchThreads, "a thread per column of the strip and its halo");
+
+// Segments of `rows` rows: first full_blocks workgroups on the full strips,
+// one segment each; then those of the narrower last strip, whose segments
+// take `lanes` threads (whole waves) and share a workgroup.
+struct MarchGrid {
+  unsigned full_blocks, segs;  // segs: per strip
+  Divisor full, lanes;         // full: full strips
+  int rows;
+};
+
+template <bool kStream>
+__global__ __launch_bounds__(kMarchThreads) void march_kernel(const float* __restrict__ src, float* __restrict__ dst,
+                                                              int nx, int ny, MarchGrid grid, Coef<float> c) {
+  constexpr int W = kMarchThreads + 2;  // thread X at X + 1
+  __shared__ float s1[4][W], s2[4][W];  // densities at t, t + 1
+  // populations at t + 1 where they arrive, by velocity: along the row, down, up
+  __shared__ float gh[4][3][W], gu[4][3][W], gd[2][3][W];
+  const int X = threadIdx.x;
+  unsigned strip, lane = X;
+  unsigned seg = div_mod(blockIdx.x, grid.full, strip);
+  if (blockIdx.x >= grid.full_blocks) {
+    strip = grid.full.d;
+    const unsigned part = __builtin_amdgcn_readfirstlane(div_mod((unsigned)X, grid.lanes, lane));
+    const unsigned parts = (unsigned)kMarchThreads / grid.lanes.d;
+    seg = part < parts ? (blockIdx.x - grid.full_blocks) * parts + part : ~0u;
+  }
+  const int x0 = (int)strip * kMarchCols, w = min(kMarchCols, nx - x0);
+  // waves past the strip or the lattice leave; barriers wait for the others only
+  if (seg >= grid.segs || __builtin_amdgcn_readfirstlane(lane) >= (unsigned)(kMarchLeft + w + 3)) return;
+  const int y0 = (int)seg * grid.rows, h = min(grid.rows, ny - y0);
+  const int x = x0 - kMarchLeft + (int)lane;
+  const size_t rowb = (size_t)36 * nx;
+  const unsigned pb = 4u * (unsigned)nx;
+  // byte offsets of the column and its neighbours
+  unsigned oc = 4u * (unsigned)wrap(x, nx), om = 4u * (unsigned)wrap(x - 1, nx), op = 4u * (unsigned)wrap(x + 1, nx);
+  const bool own = lane >= (unsigned)kMarchLeft && lane < (unsigned)(kMarchLeft + w);
+  const char* const base = reinterpret_cast<const char*>(src);
+  int yn = wrap(y0 - 2, ny);  // rows y - 1, y, y + 1 of the next row to load
+  const char* pm = base + (size_t)wrap(y0 - 4, ny) * rowb;
+  const char* p0 = base + (size_t)wrap(y0 - 3, ny) * rowb;
+  const char* pp = base + (size_t)yn * rowb;
+  char* out = reinterpret_cast<char*>(dst) + (size_t)y0 * rowb;
+  float F[4][9], G[4][9];
+  auto pull = [&](float* f) __attribute__((always_inline)) {
+    // keeps the offsets 32 bits wide beside a scalar base
+    asm volatile("" : "+v"(oc), "+v"(om), "+v"(op));
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+      f[i] = ldb<float>((kCy[i] == 0 ? p0 : (kCy[i] > 0 ? pm : pp)) + (size_t)i * pb,
+                        kCx[i] == 0 ? oc : (kCx[i] > 0 ? om : op));
+    pm = p0;
+    p0 = pp;
+    yn = yn + 1 == ny ? 0 : yn + 1;
+    pp = yn == 0 ? base : pp + rowb;
+  };
+  auto collide = [&](float* f, const float (&s)[4][W], int row) __attribute__((always_inline)) {
+    float nb[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) nb[i] = s[(row + kCy[i]) & 3][X + 1 + kCx[i]];
+    float gx, gy;
+    stencil(nb[1], nb[2], nb[3], nb[4], nb[5], nb[6], nb[7], nb[8], gx, gy);
+    collide_node<float>(f, nb[0], gx, gy, c);
+  };
+  auto iteration = [&](auto slot, int m) __attribute__((always_inline)) {
+    constexpr int I = decltype(slot)::value;
+    if (m >= 3 && m <= h + 6) {
+      float* const f = F[(I + 2) & 3];
+      collide(f, s1, I + 2);
+      gh[(I + 2) & 3][0][X + 1] = f[0];
+      gh[(I + 2) & 3][1][X + 2] = f[1];
+      gh[(I + 2) & 3][2][X] = f[3];
+      gu[(I + 3) & 3][0][X + 1] = f[2];
+      gu[(I + 3) & 3][1][X + 2] = f[5];
+      gu[(I + 3) & 3][2][X] = f[6];
+      gd[(I + 1) & 1][0][X + 1] = f[4];
+      gd[(I + 1) & 1][1][X] = f[7];
+      gd[(I + 1) & 1][2][X + 2] = f[8];
+    }
+    if (m <= h + 5) s1[I][X + 1] = density(F[I]);
+    if (m <= h + 4) pull(F[(I + 1) & 3]);
+    if (m >= 9 && m <= h + 8) {
+      float* const f = G[(I + 2) & 3];
+      collide(f, s2, I + 2);
+      // the nine rows of populations as one buffer; halo columns store outside it, that is nowhere
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc(out, 0, 9u * pb, 0x00020000);
+      asm volatile("" : "+v"(oc));
+      const unsigned so = own ? oc : 0xfffffffcu;
+#pragma unroll
+      for (int i = 0; i < 9; ++i)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f[i]), rs, so, i * pb, kStream ? 2 : 0);
+      out += rowb;
+    }
+    if (m >= 6 && m <= h + 7) {
+      float* const g = G[I];
+      g[0] = gh[I][0][X + 1];
+      g[1] = gh[I][1][X + 1];
+      g[3] = gh[I][2][X + 1];
+      g[2] = gu[I][0][X + 1];
+      g[5] = gu[I][1][X + 1];
+      g[6] = gu[I][2][X + 1];
+      g[4] = gd[I & 1][0][X + 1];
+      g[7] = gd[I & 1][1][X + 1];
+      g[8] = gd[I & 1][2][X + 1];
+      s2[I][X + 1] = density(g);
+    }
+    __syncthreads();
+  };
+  pull(F[0]);
+  for (int m = 0; m < h + 9; m += 4) {
+    iteration(std::integral_constant<int, 0>{}, m);
+    iteration(std::integral_constant<int, 1>{}, m + 1);
+    iteration(std::integral_constant<int, 2>{}, m + 2);
+    iteration(std::integral_constant<int, 3>{}, m + 3);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Several time steps per launch on small lattices (every storage).  A
 // workgroup advances a TX x TY tile by k <= K steps.  Each thread owns one
 // node of the tile plus a ring of 2 k - 1 nodes, numbered from the inside
@@ -1939,6 +2093,15 @@ bool stream_stores(unsigned long long bytes, unsigned long long row, unsigned lo
   return aligned && 2 * bytes > most;
 }
 
+// Call fn with v as std::bool_constant.
+template <class Fn>
+void with_bool(bool v, Fn&& fn) {
+  if (v)
+    fn(std::true_type{});
+  else
+    fn(std::false_type{});
+}
+
 // Call fn(stream, reverse) for one launch (or the launches of one step):
 // stream as std::bool_constant, and whether the tiles run backwards, which
 // cached launches do every other time.
@@ -2068,8 +2231,58 @@ bool mid_tile_first(const lbm_ctx* ctx) {
   return 73 * mid < 100 * large;
 }
 
+// Launch of march_kernel: as many segments as give every CU `rounds`
+// workgroups in turn, the number of rounds that costs the fewest iterations.
+struct MarchPlan {
+  int rounds, rows, segs, blocks, lanes;
+};
+constexpr int kMarchFill = 8;  // rows that filling and draining a segment's pipeline costs
+
+MarchPlan march_plan(int nx, int ny, int cus) {
+  const int full = nx / kMarchCols, rest = nx % kMarchCols;
+  const int lanes = rest ? (rest + kMarchLeft + 3 + 63) / 64 * 64 : kMarchThreads, parts = kMarchThreads / lanes;
+  MarchPlan best{0, 0, 0, 0, lanes};
+  long long least = 0;
+  for (int r = 1; r <= 4; ++r)
+    for (int rows = (int)((long long)ny * full / ((long long)r * cus)) + 1; rows <= ny; ++rows) {
+      const int segs = (ny + rows - 1) / rows;
+      const long long blocks = (long long)full * segs + (rest ? (segs + parts - 1) / parts : 0);
+      if (blocks > (long long)r * cus) continue;
+      const long long cost = (long long)r * (rows + kMarchFill);
+      if (best.rounds == 0 || cost < least) best = {r, rows, segs, (int)blocks, lanes}, least = cost;
+      break;
+    }
+  return best;
+}
+
+// Whether march_kernel takes the two steps: a full strip, and iterations that
+// would advance at most 1.25 times the lattice's nodes if every CU spent each
+// on a full row of a strip.  Measured, that ratio and us per step, step2_kernel
+// / march_kernel: 16384 x 8192 1.07 1107 / 1016, 8192^2 1.10 543 / 499, 4096^2
+// 1.14 144.2 / 137.4, 1000 x 20000 1.19 180 / 177, 3072^2 1.25 87.7 / 86.3,
+// 2560^2 1.46 64.9 / 67.8, 2048^2 1.52 41.4 / 43.2.
+bool use_march(const lbm_ctx* ctx, MarchPlan& plan) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
+  const long long nodes = (long long)nx * ny, row = (long long)cus * kMarchCols;  // row: nodes an iteration advances
+  if (nx < kMarchCols || nodes < 4 * kMarchFill * row) return false;
+  plan = march_plan(nx, ny, cus);
+  return plan.rounds && 4 * plan.rounds * (plan.rows + kMarchFill) * row <= 5 * nodes;
+}
+
+void launch_march(lbm_ctx* ctx, const MarchPlan& plan, const void* src, void* dst) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny, full = nx / kMarchCols;
+  const MarchGrid grid{(unsigned)(full * plan.segs), (unsigned)plan.segs, make_divisor((unsigned)full),
+                       make_divisor((unsigned)plan.lanes), plan.rows};
+  with_bool(stream_stores(36ull * nx * ny, 4ull * nx, kCachedAlu), [&](auto stream) {
+    march_kernel<decltype(stream)::value><<<plan.blocks, kMarchThreads, 0, ctx->stream>>>(
+        static_cast<const float*>(src), static_cast<float*>(dst), nx, ny, grid, ctx->c);
+  });
+}
+
 template <bool kMid>
 void launch_step2(lbm_ctx* ctx, const void* src, void* mid, void* dst) {
+  if constexpr (!kMid)
+    if (MarchPlan plan; use_march(ctx, plan)) return launch_march(ctx, plan, src, dst);
   if (mid_tile_first(ctx))
     launch_step2_on<Step2Mid, kMid>(ctx, src, mid, dst);
   else
@@ -2121,15 +2334,6 @@ int set_device(const lbm_ctx* ctx) {
 // Workgroups of one node per thread; lbm_create admits 9 nx ny < 2^31, so
 // the count fits a grid dimension.
 unsigned grid1(size_t n) { return static_cast<unsigned>((n + BLK - 1) / BLK); }
-
-// Call fn with v as std::bool_constant.
-template <class Fn>
-void with_bool(bool v, Fn&& fn) {
-  if (v)
-    fn(std::true_type{});
-  else
-    fn(std::false_type{});
-}
 
 // Call fn(wide, stream) for a kernel that writes (or, with stream unused,
 // reads) a whole state: 64-bit addresses for FP32 states above 4 GiB, and the
