@@ -817,19 +817,18 @@ __global__ __launch_bounds__(S::NTHREADS) void step2_kernel(const float* __restr
 //
 // What bounds it: the vector ALU, as in step2_kernel, but without that
 // kernel's halo of a 64 x 24 tile (12 % more collisions), its side nodes,
-// row tests and addresses: 460 instructions per thread and iteration, the
-// arithmetic of two updates, against 283 per update.  An iteration of 16
-// waves takes 3.35 us, 97 % of what the ALU allows.  One workgroup of 1024
-// threads per CU: its barrier keeps the waves of a SIMD together, where four
-// workgroups of 256 drift apart and leave it to the slowest at the end
-// (4096^2: 147 us per step), and its strip has the fewest partial lines.
-// The 32 columns left of the strip put the first thread's loads and the
-// stores on 128-byte lines (8192^2: 495 us; with 16 columns more of the 1024
-// threads stored, 503).  A segment costs about eight rows more than it
-// has: the pipeline fills (16 us for the first eight iterations) and drains.
-// Measured, us per step, step2_kernel / this: 3072^2 87.7 / 86.3, 5000 x 3000
-// 143 / 132, 4096^2 144.2 / 137.4, 4097 x 4093 156 / 146, 6000 x 5000 267 / 240,
-// 8192^2 543 / 499, 16384 x 8192 1107 / 1016.
+// row tests and addresses: 254 instructions per update at 4096^2 against 283
+// (and 230 of arithmetic).  One workgroup of 1024 threads per CU: its barrier
+// keeps the waves of a SIMD together, where four workgroups of 256 drift
+// apart and leave the SIMD to the slowest at the end (4096^2: 147 us per
+// step), and a wide strip has few partial lines.  The 32 columns left of the
+// strip put the first thread's loads and the stores on 128-byte lines
+// (16384 x 8192: 972 us; with 16 columns, storing 992 of the 1024, 1006).  A
+// segment costs about eight rows more than it has, while the pipeline fills
+// (16 us for its first eight iterations of 3.3) and drains.
+// Measured, us per step, step2_kernel / this: 2880^2 79.0 / 76.1, 3072^2 86.7
+// / 83.2, 5000 x 3000 142.9 / 126.4, 4096^2 142.9 / 131.9, 4097 x 4093 155.3 /
+// 138.4, 6000 x 5000 266.6 / 229.7, 8192^2 542 / 487, 16384 x 8192 1103 / 975.
 // ---------------------------------------------------------------------------
 constexpr int kMarchThreads = 1024, kMarchLeft = 32, kMarchCols = 960;
 static_assert(kMarchLeft + kMarchCols + 3 <= kMarchThreads, "a thread per column of the strip and its halo");
@@ -875,6 +874,10 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(const float* __res
   const char* p0 = base + (size_t)wrap(y0 - 3, ny) * rowb;
   const char* pp = base + (size_t)yn * rowb;
   char* out = reinterpret_cast<char*>(dst) + (size_t)y0 * rowb;
+  unsigned xb = 4u * (unsigned)X;  // byte offset of the thread's column within an LDS row
+  auto at = [&](float* row, int d) __attribute__((always_inline)) -> float& {
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(row) + 4 * (d + 1) + xb);
+  };
   float F[4][9], G[4][9];
   auto pull = [&](float* f) __attribute__((always_inline)) {
     // keeps the offsets 32 bits wide beside a scalar base
@@ -888,30 +891,34 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(const float* __res
     yn = yn + 1 == ny ? 0 : yn + 1;
     pp = yn == 0 ? base : pp + rowb;
   };
-  auto collide = [&](float* f, const float (&s)[4][W], int row) __attribute__((always_inline)) {
+  auto collide = [&](float* f, float (&s)[4][W], int row) __attribute__((always_inline)) {
     float nb[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) nb[i] = s[(row + kCy[i]) & 3][X + 1 + kCx[i]];
+    for (int i = 0; i < 9; ++i) nb[i] = at(s[(row + kCy[i]) & 3], kCx[i]);
     float gx, gy;
     stencil(nb[1], nb[2], nb[3], nb[4], nb[5], nb[6], nb[7], nb[8], gx, gy);
     collide_node<float>(f, nb[0], gx, gy, c);
   };
   auto iteration = [&](auto slot, int m) __attribute__((always_inline)) {
     constexpr int I = decltype(slot)::value;
+    // LDS addresses are formed in every iteration: kept across iterations they
+    // take 12 registers, three more than there are (16 waves: 128), and the
+    // spills' traffic costs 3 % (4096^2: 134.6 / 131.1 us per step)
+    asm volatile("" : "+v"(xb));
     if (m >= 3 && m <= h + 6) {
       float* const f = F[(I + 2) & 3];
       collide(f, s1, I + 2);
-      gh[(I + 2) & 3][0][X + 1] = f[0];
-      gh[(I + 2) & 3][1][X + 2] = f[1];
-      gh[(I + 2) & 3][2][X] = f[3];
-      gu[(I + 3) & 3][0][X + 1] = f[2];
-      gu[(I + 3) & 3][1][X + 2] = f[5];
-      gu[(I + 3) & 3][2][X] = f[6];
-      gd[(I + 1) & 1][0][X + 1] = f[4];
-      gd[(I + 1) & 1][1][X] = f[7];
-      gd[(I + 1) & 1][2][X + 2] = f[8];
+      at(gh[(I + 2) & 3][0], 0) = f[0];
+      at(gh[(I + 2) & 3][1], 1) = f[1];
+      at(gh[(I + 2) & 3][2], -1) = f[3];
+      at(gu[(I + 3) & 3][0], 0) = f[2];
+      at(gu[(I + 3) & 3][1], 1) = f[5];
+      at(gu[(I + 3) & 3][2], -1) = f[6];
+      at(gd[(I + 1) & 1][0], 0) = f[4];
+      at(gd[(I + 1) & 1][1], -1) = f[7];
+      at(gd[(I + 1) & 1][2], 1) = f[8];
     }
-    if (m <= h + 5) s1[I][X + 1] = density(F[I]);
+    if (m <= h + 5) at(s1[I], 0) = density(F[I]);
     if (m <= h + 4) pull(F[(I + 1) & 3]);
     if (m >= 9 && m <= h + 8) {
       float* const f = G[(I + 2) & 3];
@@ -927,16 +934,16 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(const float* __res
     }
     if (m >= 6 && m <= h + 7) {
       float* const g = G[I];
-      g[0] = gh[I][0][X + 1];
-      g[1] = gh[I][1][X + 1];
-      g[3] = gh[I][2][X + 1];
-      g[2] = gu[I][0][X + 1];
-      g[5] = gu[I][1][X + 1];
-      g[6] = gu[I][2][X + 1];
-      g[4] = gd[I & 1][0][X + 1];
-      g[7] = gd[I & 1][1][X + 1];
-      g[8] = gd[I & 1][2][X + 1];
-      s2[I][X + 1] = density(g);
+      g[0] = at(gh[I][0], 0);
+      g[1] = at(gh[I][1], 0);
+      g[3] = at(gh[I][2], 0);
+      g[2] = at(gu[I][0], 0);
+      g[5] = at(gu[I][1], 0);
+      g[6] = at(gu[I][2], 0);
+      g[4] = at(gd[I & 1][0], 0);
+      g[7] = at(gd[I & 1][1], 0);
+      g[8] = at(gd[I & 1][2], 0);
+      at(s2[I], 0) = density(g);
     }
     __syncthreads();
   };
@@ -2256,17 +2263,18 @@ MarchPlan march_plan(int nx, int ny, int cus) {
 }
 
 // Whether march_kernel takes the two steps: a full strip, and iterations that
-// would advance at most 1.25 times the lattice's nodes if every CU spent each
+// would advance at most 1.3 times the lattice's nodes if every CU spent each
 // on a full row of a strip.  Measured, that ratio and us per step, step2_kernel
-// / march_kernel: 16384 x 8192 1.07 1107 / 1016, 8192^2 1.10 543 / 499, 4096^2
-// 1.14 144.2 / 137.4, 1000 x 20000 1.19 180 / 177, 3072^2 1.25 87.7 / 86.3,
-// 2560^2 1.46 64.9 / 67.8, 2048^2 1.52 41.4 / 43.2.
+// / march_kernel: 16384 x 8192 1.07 1103 / 975, 8192^2 1.10 542 / 487, 4096^2
+// 1.14 142.9 / 131.9, 1000 x 20000 1.19 177.0 / 168.3, 2880^2 1.24 79.0 / 76.1,
+// 3000^2 1.26 86.2 / 82.2, 960 x 8192 1.28 72.8 / 73.0, 2700^2 1.35 70.7 / 69.8,
+// 2304^2 1.44 53.4 / 52.2, 2560^2 1.46 63.9 / 64.5, 2048^2 1.52 40.1 / 40.1.
 bool use_march(const lbm_ctx* ctx, MarchPlan& plan) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
   const long long nodes = (long long)nx * ny, row = (long long)cus * kMarchCols;  // row: nodes an iteration advances
-  if (nx < kMarchCols || nodes < 4 * kMarchFill * row) return false;
+  if (nx < kMarchCols || 3 * nodes < 10 * kMarchFill * row) return false;
   plan = march_plan(nx, ny, cus);
-  return plan.rounds && 4 * plan.rounds * (plan.rows + kMarchFill) * row <= 5 * nodes;
+  return plan.rounds && 10 * plan.rounds * (plan.rows + kMarchFill) * row <= 13 * nodes;
 }
 
 void launch_march(lbm_ctx* ctx, const MarchPlan& plan, const void* src, void* dst) {
