@@ -214,7 +214,7 @@ def step_leg(pkg, wl, timer, storage, n, steps, warmup, tr=0.7, width=10.0, sing
     kernel = "step2_f32" if two_step else "step_" + storage.replace("fp", "f")
     traffic = measured_traffic(kernel, n * n)
     return d, rho0, {"mlups": mlups, "ms_per_step": round(per, 5),
-                     "kernel": ("step2_kernel<F32>, two steps per launch" if two_step
+                     "kernel": ("march_kernel<F32>, two steps per launch" if two_step
                                 else f"step_kernel<{storage.upper()}>, one step per launch"),
                      "achieved_gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
                      "algorithmic_bytes_per_lu": alg,
