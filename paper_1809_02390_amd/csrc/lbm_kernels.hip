@@ -923,10 +923,10 @@ __global__ __launch_bounds__(kMarchThreads) void march_kernel(const float* __res
     if (m >= 9 && m <= h + 8) {
       float* const f = G[(I + 2) & 3];
       collide(f, s2, I + 2);
-      // the nine rows of populations as one buffer; halo columns store outside it, that is nowhere
+      // the nine rows of populations as one buffer; halo columns store beyond its end, that is nowhere
       const auto rs = __builtin_amdgcn_make_buffer_rsrc(out, 0, 9u * pb, 0x00020000);
       asm volatile("" : "+v"(oc));
-      const unsigned so = own ? oc : 0xfffffffcu;
+      const unsigned so = own ? oc : 1u << 31;
 #pragma unroll
       for (int i = 0; i < 9; ++i)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f[i]), rs, so, i * pb, kStream ? 2 : 0);
