@@ -1324,8 +1324,12 @@ __device__ __forceinline__ void put_node(int x, int y, int nx, int ny, const flo
 
 // One thread per node o of the lattice, in row order; width: make_divisor(nx).
 // These kernels move 40 (init), 72 (set, get) or 80 (adjoint seed) bytes per
-// node and are bound by HBM, with streamed stores where stream_stores says
-// so.
+// node and are bound by HBM.  Their store policy is stream_whole, except
+// where put_node stores rows shifted by the streaming and the cached lines
+// merge them better: FP32 initial states with velocities (us, streamed /
+// cached: 2880^2 108 / 93, 3600^2 183 / 144, 8192^2 667 / 651; 2-byte 3200^2
+// 74 / 87, 4096^2 111 / 124, streamed) and loaded 2-byte states (4000^2 188 /
+// 167, 8192^2 766 / 732).
 constexpr int BLK = 256;
 __device__ __forceinline__ bool flat_node(int nx, int ny, const Divisor& width, unsigned& o, int& x, int& y) {
   o = blockIdx.x * BLK + threadIdx.x;
@@ -1441,8 +1445,11 @@ __global__ __launch_bounds__(InitTile<St>::NTHREADS) void init_rest_kernel(const
   }
 }
 
-// Load a post-streaming state (FP32 with the shift in the loads, us against
-// in the stores: 512^2 3.6 / 4.3, 4096^2 199 / 233, 16384 x 8192 1608 / 1805).
+// Load a post-streaming state.  FP32 states past the caches with the shift in
+// the loads, so that whole rows are streamed (us against shifted stores:
+// 2400^2 62 / 77, 4096^2 199 / 218, 8192^2 816 / 920); smaller ones with the
+// shift in the stores, which the caches merge (in the loads / in the stores:
+// 760^2 7.3 / 6.75, 1000^2 12.5 / 12.0, 300 x 2800 11.3 / 10.6).
 template <class St, bool kWideAddr, bool kStream>
 __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict__ fin, void* __restrict__ dst,
                                                         uint16_t* __restrict__ ref_out, int nx, int ny, Divisor width,
@@ -1451,9 +1458,8 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
   int x, y;
   if (!flat_node(nx, ny, width, o, x, y)) return;
   const Planes<float> F = planes<float>(fin, (size_t)nx * ny);
-  if constexpr (!St::kRef) {
-    // a permutation: slot (i, x) is f_i of node x + e_i.  The shift goes into
-    // the loads, so that whole rows are stored.
+  if constexpr (!St::kRef && kStream) {
+    // a permutation: slot (i, x) is f_i of node x + e_i
     const Layout L = state_layout(nx, ny, 4);
     const NodeAddr<4> a = node_addr<4>(x, y, nx, ny, (unsigned)nx);
     char* const base = static_cast<char*>(dst) + (kWideAddr ? (size_t)y * L.rp * 4 : 0);
@@ -1461,13 +1467,13 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       const unsigned from = (kCy[i] == 0 ? a.r0 : (kCy[i] > 0 ? a.rp : a.rm)) + (kCx[i] == 0 ? a.c0 : (kCx[i] > 0 ? a.cp : a.cm));
-      put<kStream>(ldb<float>(F.p[i], from), base + (size_t)i * L.ps * 4, off);
+      put<true>(ldb<float>(F.p[i], from), base + (size_t)i * L.ps * 4, off);
     }
   } else {
     float f[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) f[i] = ldb<float>(F.p[i], 4u * o);
-    put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
+    put_node<St, kWideAddr, false>(x, y, nx, ny, f, q, dst, ref_out);
   }
 }
 
@@ -2100,6 +2106,17 @@ bool stream_stores(unsigned long long bytes, unsigned long long row, unsigned lo
   return aligned && 2 * bytes > most;
 }
 
+// The same for the kernels of one node per thread that write a whole state
+// (initial, loaded and seeded states): only states past the caches.  Smaller
+// ones are read next by another kernel, and rows shorter than a workgroup
+// share their lines with other rows, which streamed stores then write in
+// parts (us, streamed / cached: FP32 set_state 3 x 100000 17.5 / 7.6, 10 x
+// 34000 8.3 / 5.4, 600^2 4.6 / 4.3; adjoint seed 3 x 100000 23.8 / 8.9, 380^2
+// 3.8 / 3.4; but seed 2048^2 48 / 65, 2400^2 65 / 80).
+bool stream_whole(unsigned long long bytes, unsigned long long row) {
+  return bytes >= 16ull << 20 && stream_stores(bytes, row, kCachedHbm);
+}
+
 // Call fn with v as std::bool_constant.
 template <class Fn>
 void with_bool(bool v, Fn&& fn) {
@@ -2349,7 +2366,7 @@ unsigned grid1(size_t n) { return static_cast<unsigned>((n + BLK - 1) / BLK); }
 template <class St, class Fn>
 void with_state_access(const lbm_ctx* ctx, Fn&& fn) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
-  with_bool(stream_stores(9ull * St::ES * nx * ny, (unsigned long long)St::ES * nx, kCachedHbm), [&](auto stream) {
+  with_bool(stream_whole(9ull * St::ES * nx * ny, (unsigned long long)St::ES * nx), [&](auto stream) {
     if constexpr (St::kRef)
       fn(std::false_type{}, stream);
     else
@@ -2368,7 +2385,7 @@ void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const 
     using S = InitTile<St>;
     const unsigned long long row = 9ull * St::ES * nx;
     if constexpr (decltype(stream)::value)
-      if (rest && row * ny >= 16ull << 20 && row * S::TY < 1ull << 32) {
+      if (rest && row * S::TY < 1ull << 32) {
         const int ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
         init_rest_kernel<St><<<nt, dim3(S::TX, S::WY), 0, ctx->stream>>>(
             rho0, ctx->buf[0], ctx->ref[0], nx, ny, make_order(ntx, nt / ntx, strip_width(nx, S::TX, false), false),
@@ -2376,7 +2393,7 @@ void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const 
         return;
       }
     with_bool(rest, [&](auto r) {
-      init_kernel<St, decltype(wide)::value, decltype(stream)::value, decltype(r)::value>
+      init_kernel<St, decltype(wide)::value, St::kRef && decltype(stream)::value, decltype(r)::value>
           <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(rho0, ux0, uy0, ctx->buf[0], ctx->ref[0], nx, ny,
                                                            make_divisor(nx), ctx->c, ctx->q, flag);
     });
@@ -2519,7 +2536,7 @@ int lbm_set_state(lbm_ctx* ctx, const float* f) {
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
     with_state_access<St>(ctx, [&](auto wide, auto stream) {
-      set_state_kernel<St, decltype(wide)::value, decltype(stream)::value>
+      set_state_kernel<St, decltype(wide)::value, !St::kRef && decltype(stream)::value>
           <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], nx, ny, make_divisor(nx),
                                                            ctx->q);
     });
@@ -2757,7 +2774,7 @@ int lbm_adjoint_seed(lbm_ctx* ctx, const float* lam, void* adj) {
   if (!lam || !adj) return fail(LBM_EINVAL, "lam and adj must be device buffers");
   if (int st = set_device(ctx)) return st;
   const int nx = ctx->p.nx, ny = ctx->p.ny;
-  with_bool(stream_stores(44ull * nx * ny, 4ull * nx, kCachedHbm), [&](auto stream) {
+  with_bool(stream_whole(44ull * nx * ny, 4ull * nx), [&](auto stream) {
     adjoint_seed_kernel<decltype(stream)::value><<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(
         lam, static_cast<float*>(adj), nx, ny, make_divisor(nx));
   });

@@ -1,0 +1,89 @@
+"""Calls that choose between kernels or store policies, timed against another
+call of the same lattice that bounds their cost: a choice that loses to the
+simpler one shows as a ratio.  Each limit lies between the ratio of the better
+choice and that of the worse one (both given with the case); a ratio has to
+exceed it in three measurements to fail."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1809_02390_amd as pkg
+import workloads as wl
+from paper_1809_02390_amd import lbm as L
+from tests._gpu_helpers import params_pair
+
+pytestmark = pytest.mark.gpu
+
+
+def _lat(nx, ny, storage="fp32"):
+    _, co = params_pair(nx, ny, tr=0.7)
+    rho = torch.as_tensor(wl.uniform_noise(nx, ny, 0.5 * (co.rho_g + co.rho_l), 0.01, seed=nx), dtype=torch.float32,
+                          device="cuda")
+    return rho, pkg.Lattice(nx, ny, tr=0.7, storage=storage).init(rho)
+
+
+def _cost(call, repeat):
+    """Device time of one of `repeat` calls in a row (ms)."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    for _ in range(repeat):
+        call()
+    b.record()
+    b.synchronize()
+    return a.elapsed_time(b) / repeat
+
+
+def _ratio(call, bound, repeat):
+    """Median cost of call over that of bound, nine measurements in turn."""
+    call(), bound()
+    t = np.array([[_cost(call, repeat), _cost(bound, repeat)] for _ in range(9)])
+    return float(np.median(t[:, 0]) / np.median(t[:, 1]))
+
+
+def _assert_ratio(call, bound, limit, repeat=20):
+    got = [_ratio(call, bound, repeat)]
+    while got[-1] > limit and len(got) < 3:
+        got.append(_ratio(call, bound, repeat))
+    assert got[-1] <= limit, got
+
+
+def test_short_rows_are_not_stored_in_parts():
+    """3 x 100000 (rows of 12 bytes): loading a state and seeding an adjoint
+    against exporting a state, which moves the same 72 bytes per node; cached
+    1.5 and 1.7 times its cost, the adjoint streamed 5.3."""
+    nx, ny = 3, 100000
+    _, lat = _lat(nx, ny)
+    f = lat.state()
+    adj, out = lat.adjoint_buffer(), torch.empty_like(f)
+    get = lambda: L.lbm_get_state(lat.ctx, out, lat.n)
+    nb = L.lbm_adjoint_bytes(lat.params)
+    _assert_ratio(lambda: L.lbm_set_state(lat.ctx, f, lat.n), get, 2.3)
+    _assert_ratio(lambda: L.lbm_adjoint_seed(lat.ctx, f, adj, lat.n, nb), get, 2.8)
+    lat.close()
+
+
+def test_shifted_rows_are_merged_in_the_caches():
+    """3600^2: an initial state with velocities (48 bytes per node) against
+    loading a state (72); cached 0.92 of its cost, streamed 1.16."""
+    n = 3600
+    rho, lat = _lat(n, n)
+    u = torch.full_like(rho, 0.01)
+    f = lat.state()
+    _assert_ratio(lambda: L.lbm_init(lat.ctx, rho, u, u, lat.n), lambda: L.lbm_set_state(lat.ctx, f, lat.n), 1.05, 5)
+    lat.close()
+
+
+# FP32: below and above the size from which states are streamed (row length a
+# multiple of 64 bytes and a state above 144 MiB), and rows off 64 bytes.
+@pytest.mark.parametrize("nx,ny", [(3, 1000), (560, 600), (2064, 2031), (2064, 2040), (2101, 2048)])
+def test_loaded_states_agree(nx, ny):
+    """A loaded state is exported unchanged, and a state at zero velocity
+    given as populations equals the initial one, bit for bit."""
+    rho, lat = _lat(nx, ny)
+    zero = torch.zeros_like(rho)
+    used = 36 * nx * ny
+    first = lat.init(rho, zero, zero).save_state()[:used]
+    f = lat.state()
+    assert torch.equal(lat.set_state(f).save_state()[:used], first)
+    assert torch.equal(lat.state(), f)
+    lat.close()
