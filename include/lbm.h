@@ -162,7 +162,7 @@ int lbm_get_state(lbm_ctx* ctx, float* f);
  * and B.  Each step fuses the
  * density halo, the force, the collision and the streaming.  Small lattices
  * take up to four steps per kernel launch in every storage (LBM_FP32 up to
- * about 730^2 nodes, 2-byte 590^2; tiles of 4 x 4, 8 x 8, 32 x 8 or 16 x 16
+ * about 440^2 nodes, 2-byte 590^2; tiles of 4 x 4, 8 x 8, 32 x 8 or 16 x 16
  * nodes by size); larger LBM_FP32 lattices (up to about 3.7M nodes wide) two
  * (tiles of 64 x 24 or 64 x 16 nodes; from about 2800^2 on, strips of 960
  * columns walked row by row), then one step for an odd remainder; larger

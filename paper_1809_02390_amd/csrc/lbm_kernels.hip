@@ -2206,12 +2206,32 @@ using StepKSmall = TileKShape<8, 8, 4>;
 using StepKWide = TileKShape<32, 8, 3>;
 using StepKLast = TileKShape<16, 16, 2>;
 
-// Whether a lattice has just enough 64 x 16 tiles for the two-step kernel to
-// run one per CU (7/8 of the CUs to all of them), where it beats stepk_kernel
-// (512^2, us per step: 4.02 against 4.52).
-bool one_mid_tile_per_cu(const lbm_ctx* ctx) {
-  const int t = tiles_total<Step2Mid>(ctx->p.nx, ctx->p.ny);
-  return t <= ctx->cus && 8 * t > 7 * ctx->cus;
+// 16 x 16 tiles per CU, in tenths, up to which stepk_kernel advances an FP32
+// lattice two steps faster than the two-step kernel, whose time goes by the
+// turns the CUs take through its tiles.  Measured, us per 20 steps, 16 x 16 /
+// 64 x 16 / 64 x 24 tiles, 16 x 16 tiles per CU in brackets:
+//  - at most one 64 x 16 tile per CU: 400^2 (2.4) 77 / 82 / 99, 432^2 (2.8) 78
+//    / 82 / 98, 6000 x 24 (2.9) 97 / 89 / 95, 448^2 (3.1) 86 / 83 / 99, 2000 x
+//    112 (3.4) 98 / 84 / 97, 512^2 (4.0) 93 / 81 / 98;
+//  - else one 64 x 24 tile: 520^2 (4.3) 104 / 120 / 105, 544^2 (4.5) 107 / 112
+//    / 97, 100 x 3000 (5.1) 112 / 111 / 98, 600^2 (5.6) 120 / 111 / 98, 16000 x
+//    24 (7.8) 164 / 131 / 106;
+//  - else two 64 x 16 tiles: 72 x 3400 (4.2) 100 / 121 / 155, 20000 x 5 (4.9)
+//    87 / 91 / 110, 608^2 (5.6) 120 / 111 / 142, 200 x 1800 (5.7) 118 / 121 /
+//    154, 700^2 (7.6) 151 / 130 / 160;
+//  - else: 712^2 (7.9) 161 / 171 / 160, 740^2 (8.6) 164 / 167 / 163.
+// Storing every state as well (us for 8 steps): 380^2 (2.3) 31.3 / 32.2 / 38.6,
+// 400^2 (2.4) 35.0 / 33.3 / 41.0; 544^2 (4.5) 47.6 / 50.9 / 44.8, 600^2 (5.6)
+// 53.7 / 52.6 / 59.5, 620^2 (5.9) 54.5 / 58.2 / 68.0, 660^2 (6.9) 64.5 / 64.5 /
+// 71.0.
+template <bool kChain>
+int last_tile_limit(const lbm_ctx* ctx) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
+  const int mid = tiles_total<Step2Mid>(nx, ny);
+  if (kChain) return mid <= cus ? 23 : 65;
+  if (mid <= cus) return 29;
+  if (tiles_total<Step2Tile>(nx, ny) <= cus) return 42;
+  return mid <= 2 * cus ? 55 : 85;
 }
 
 // The tile of stepk_kernel (1 .. 4, in the order above), or 0 where the
@@ -2224,12 +2244,9 @@ bool one_mid_tile_per_cu(const lbm_ctx* ctx) {
 //         350^2 9.26 / 4.06 / 2.77 / 3.23 / 3.54    400^2 11.6 / 4.94 / 3.97 / 3.70 / 4.18
 //   FP16  64^2 1.66 / 1.80 / 2.23 / 2.61 / 4.06    256^2 9.3 / 3.39 / 2.40 / 2.76 / 3.59
 //         350^2 16.4 / 5.43 / 3.17 / 3.56 / 4.86    400^2 20.8 / 6.59 / 4.31 / 4.16 / 5.08
-// The last tile ends where the kernels with larger tiles fill the chip
-// (16 x 16 / without): FP32 512^2 4.52 / 4.02 (one 64 x 16 tile per CU),
-// 620^2 5.98 / 7.07, 700^2 7.46 / 8.03, 800 x 700 8.26 / 8.40, 830^2 9.47 /
-// 8.58; with every state stored 640^2 8.20 / 8.67, 680^2 9.04 / 8.82; 2-byte
-// 500^2 5.06 / 5.28, 560^2 5.97 / 6.23, 600^2 6.57 / 6.27, 640^2 7.56 / 6.92,
-// 700^2 8.26 / 6.95.
+// The last tile ends where the kernels with larger tiles fill the chip: FP32
+// by last_tile_limit; 2-byte (16 x 16 / single steps) 500^2 5.2 / 5.4, 560^2
+// 6.2 / 6.4, 600^2 6.57 / 6.27, 640^2 7.56 / 6.92, 700^2 8.26 / 6.95.
 template <class St, bool kChain>
 int stepk_shape(const lbm_ctx* ctx) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
@@ -2240,7 +2257,7 @@ int stepk_shape(const lbm_ctx* ctx) {
   if constexpr (St::kRef) {
     return 2 * t <= 11 * cus ? 4 : 0;
   } else {
-    return !one_mid_tile_per_cu(ctx) && 2 * t <= (kChain ? 13 : 17) * cus ? 4 : 0;
+    return 10 * t <= last_tile_limit<kChain>(ctx) * cus ? 4 : 0;
   }
 }
 

@@ -87,3 +87,39 @@ def test_loaded_states_agree(nx, ny):
     assert torch.equal(lat.set_state(f).save_state()[:used], first)
     assert torch.equal(lat.state(), f)
     lat.close()
+
+
+def _single(lat, n):
+    for _ in range(n):
+        L.lbm_step(lat.ctx, 1)
+
+
+# 600 x 600: 250 tiles of 64 x 24; 1000 x 350: 240.
+@pytest.mark.parametrize("nx,ny", [(600, 600), (1000, 350)])
+def test_several_steps_cost_no_more_than_single_steps_fp32(nx, ny):
+    """lbm_step(20) against 20 calls of one step: 0.9 of their cost with one
+    64 x 24 two-step tile per CU, 1.1 on 16 x 16 tiles."""
+    _, lat = _lat(nx, ny)
+    _assert_ratio(lambda: L.lbm_step(lat.ctx, 20), lambda: _single(lat, 20), 1.0, 5)
+    lat.close()
+
+
+# Two steps per launch on either side of the lines between 16 x 16, 64 x 16 and
+# 64 x 24 tiles (256 CUs): 2.8 and 3.1 tiles of 16 x 16 per CU; one 64 x 16
+# tile and more; one 64 x 24 tile and more; two 64 x 16 tiles and more.
+@pytest.mark.parametrize("nx,ny", [(432, 432), (448, 448), (512, 512), (520, 520), (600, 600), (608, 608), (6000, 24),
+                                   (100, 3000), (200, 1800), (700, 700), (712, 712)])
+def test_two_step_tiles_agree(nx, ny):
+    """Three steps in one call, and as a chain of stored states, bitwise three
+    calls of one step."""
+    _, lat = _lat(nx, ny)
+    used = 36 * nx * ny
+    bufs = [lat.checkpoint_buffer().zero_() for _ in range(4)]
+    lat.save_state(bufs[0])
+    lat.step_saved_chain(bufs)
+    once = lat.step(3).save_state()[:used].clone()
+    lat.load_state(bufs[0])
+    for j in range(1, 4):
+        assert torch.equal(lat.step(1).save_state()[:used], bufs[j][:used])
+    assert torch.equal(bufs[3][:used], once)
+    lat.close()
