@@ -2246,7 +2246,14 @@ int last_tile_limit(const lbm_ctx* ctx) {
 //         350^2 16.4 / 5.43 / 3.17 / 3.56 / 4.86    400^2 20.8 / 6.59 / 4.31 / 4.16 / 5.08
 // The last tile ends where the kernels with larger tiles fill the chip: FP32
 // by last_tile_limit; 2-byte (16 x 16 / single steps) 500^2 5.2 / 5.4, 560^2
-// 6.2 / 6.4, 600^2 6.57 / 6.27, 640^2 7.56 / 6.92, 700^2 8.26 / 6.95.
+// 6.2 / 6.4, 600^2 6.57 / 6.27, 640^2 7.56 / 6.92, 700^2 8.26 / 6.95.  Single
+// 2-byte steps also win where 16 x 16 tiles hold more rows past the lattice
+// than the 64 x 8 tiles of the single step: from three tiles per CU on, more
+// than 2.2 of them per 64 x 8 tile (16 x 16 / single, tiles per CU and per 64 x
+// 8 tile in brackets): 20000 x 4 5.45 / 4.35 (4.9, 4.0), 10000 x 24 7.1 / 5.35
+// (4.9, 2.7), 4800 x 40 5.65 / 5.1 (3.5, 2.4), 3000 x 72 5.55 / 5.25 (3.7,
+// 2.2), but 4000 x 40 4.65 / 5.0 (2.9, 2.4), 5500 x 24 4.7 / 4.8 (2.7, 2.7),
+// 16000 x 9 4.95 / 6.3 (3.9, 2.0).
 template <class St, bool kChain>
 int stepk_shape(const lbm_ctx* ctx) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
@@ -2255,7 +2262,8 @@ int stepk_shape(const lbm_ctx* ctx) {
   if (tiles_total<StepKWide>(nx, ny) <= 2 * cus) return 3;
   const int t = tiles_total<StepKLast>(nx, ny);
   if constexpr (St::kRef) {
-    return 2 * t <= 11 * cus ? 4 : 0;
+    const bool sparse = t > 3 * cus && 10 * t > 22 * tiles_total<NearTile<St>>(nx, ny);
+    return !sparse && 2 * t <= 11 * cus ? 4 : 0;
   } else {
     return 10 * t <= last_tile_limit<kChain>(ctx) * cus ? 4 : 0;
   }

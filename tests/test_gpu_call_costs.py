@@ -104,6 +104,16 @@ def test_several_steps_cost_no_more_than_single_steps_fp32(nx, ny):
     lat.close()
 
 
+# 16 x 16 tiles that hold more rows past the lattice than 64 x 8 tiles do.
+@pytest.mark.parametrize("nx,ny,storage", [(20000, 4, "fp16"), (10000, 24, "bf16")])
+def test_several_steps_cost_no_more_than_single_steps_2_byte(nx, ny, storage):
+    """lbm_step(20) against 20 calls of one step: the same kernel, 1.26 and
+    1.31 of their cost on 16 x 16 tiles."""
+    _, lat = _lat(nx, ny, storage)
+    _assert_ratio(lambda: L.lbm_step(lat.ctx, 20), lambda: _single(lat, 20), 1.12, 5)
+    lat.close()
+
+
 # Two steps per launch on either side of the lines between 16 x 16, 64 x 16 and
 # 64 x 24 tiles (256 CUs): 2.8 and 3.1 tiles of 16 x 16 per CU; one 64 x 16
 # tile and more; one 64 x 24 tile and more; two 64 x 16 tiles and more.
@@ -122,4 +132,20 @@ def test_two_step_tiles_agree(nx, ny):
     for j in range(1, 4):
         assert torch.equal(lat.step(1).save_state()[:used], bufs[j][:used])
     assert torch.equal(bufs[3][:used], once)
+    lat.close()
+
+
+# 2-byte lattices on either side of the line between 16 x 16 tiles and single
+# steps: 2.2 and 2.4 tiles per 64 x 8 tile, below and above three per CU.
+@pytest.mark.parametrize("storage", ["fp16", "bf16"])
+@pytest.mark.parametrize("nx,ny", [(2000, 72), (4000, 40), (4800, 40), (20000, 4), (16000, 9)])
+def test_flat_2_byte_steps_agree(nx, ny, storage):
+    """Five steps in one call bitwise five calls of one step, the reference
+    densities included."""
+    rho, lat = _lat(nx, ny, storage)
+    once = lat.step(5).state()
+    ref = lat.save_state()[-2 * nx * ny:]
+    lat.init(rho)
+    _single(lat, 5)
+    assert torch.equal(lat.state(), once) and torch.equal(lat.save_state()[-2 * nx * ny:], ref)
     lat.close()
