@@ -2040,6 +2040,16 @@ int strip_width(int nx, int tx, bool raster) {
   const int w = nodes / tx;
   return w < 1 ? 1 : (w > ntx ? ntx : w);
 }
+
+// Tile columns per strip for the tiles of one node per thread, on an ntx x nty
+// grid where strip_width gives `strip`: at most 32, else the tile that shares
+// halo lines with the one above it comes after that XCD's L2 has let them go,
+// or on another XCD (FP32, us per step, strip_width / at most 32: 50000 x 6 8.7
+// / 6.0, 100000 x 30 42.4 / 35.2, 16384 x 200 36.2 / 36.2).  2-byte lattices
+// in raster order only if an XCD's run is less than a row of tiles, that is
+// below eight of them (20000 x 10 7.7 / 6.0, 16000 x 12 6.0 / 4.95, 6000 x 48
+// 6.23 / 6.15, but 10000 x 200 18.8 / 19.1).
+int near_strip_width(int strip, int nty, bool raster) { return strip > 32 && (!raster || nty < 8) ? 32 : strip; }
 template <class S>
 int tiles_total(int nx, int ny) { return tiles_x<S>(nx) * ((ny + S::TY - 1) / S::TY); }
 
@@ -2144,13 +2154,13 @@ void with_stores(lbm_ctx* ctx, bool stream, Fn&& fn) {
 template <class St, class S>
 void launch_step_tiles(lbm_ctx* ctx, bool stream, const void* src, void* dst, const uint16_t* ref_in,
                        uint16_t* ref_out) {
-  const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx);
+  const int nx = ctx->p.nx, ny = ctx->p.ny, ntx = tiles_x<S>(nx), strip = strip_width(nx, S::TX, St::kRef);
+  auto columns = [&](int nrows) { return S::NPT == 1 ? near_strip_width(strip, nrows, St::kRef) : strip; };
   with_stores(ctx, stream, [&](auto str, bool reverse) {
     for_tile_rows<S, !St::kRef>(nx, ny, [&](auto mode, TileRows rows, int nrows) {
       step_kernel<S, St, decltype(mode)::value, decltype(str)::value>
           <<<ntx * nrows, dim3(S::TX, S::WY), 0, ctx->stream>>>(
-              src, dst, ref_in, ref_out, nx, ny,
-              make_order(ntx, nrows, strip_width(nx, S::TX, St::kRef), reverse), ctx->c, ctx->q, rows);
+              src, dst, ref_in, ref_out, nx, ny, make_order(ntx, nrows, columns(nrows), reverse), ctx->c, ctx->q, rows);
     });
   });
 }

@@ -114,6 +114,32 @@ def test_several_steps_cost_no_more_than_single_steps_2_byte(nx, ny, storage):
     lat.close()
 
 
+def test_flat_lattices_share_halo_lines():
+    """50000 x 6, two rows of 781 tiles: a step against the export of the
+    state, which moves the same 72 bytes per node: 1.5 times its cost in
+    strips of 32 tiles, 2.2 in longer ones."""
+    _, lat = _lat(50000, 6)
+    out = lat.state()
+    _assert_ratio(lambda: L.lbm_step(lat.ctx, 1), lambda: L.lbm_get_state(lat.ctx, out, lat.n), 1.85)
+    lat.close()
+
+
+# Strips of 32 tiles of 64 nodes and a narrower last one, or a single tile
+# column beyond them; 2-byte lattices below and from eight rows of tiles on.
+@pytest.mark.parametrize("nx,ny,storage", [(2112, 9, "fp32"), (50000, 6, "fp32"), (2100, 30, "fp16"), (4100, 56, "bf16"),
+                                           (4100, 57, "bf16")])
+def test_strips_of_one_step_agree(nx, ny, storage):
+    """One step of a flat lattice, which visits its tiles in strips, bitwise
+    the repeated step of the lattice it repeats in y, visited in others."""
+    rho, lat = _lat(nx, ny, storage)
+    one = lat.step(1).state()
+    lat.close()
+    with_copies = pkg.Lattice(nx, 8 * ny, tr=0.7, storage=storage).init(rho.repeat(8, 1))
+    many = with_copies.step(1).state()
+    assert torch.equal(many, one.repeat(1, 8, 1))
+    with_copies.close()
+
+
 # Two steps per launch on either side of the lines between 16 x 16, 64 x 16 and
 # 64 x 24 tiles (256 CUs): 2.8 and 3.1 tiles of 16 x 16 per CU; one 64 x 16
 # tile and more; one 64 x 24 tile and more; two 64 x 16 tiles and more.
