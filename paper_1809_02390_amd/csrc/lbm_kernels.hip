@@ -2165,6 +2165,17 @@ void launch_step_tiles(lbm_ctx* ctx, bool stream, const void* src, void* dst, co
   });
 }
 
+// Whether one 2-byte step takes the 64 x 4 tiles of FP32: at most one 64 x 8
+// tile per two CUs, where the launch is as long as one workgroup (us, 64 x 4 /
+// 64 x 8: 64^2 3.5 / 3.7, 160^2 3.6 / 3.8, 256^2 3.65 / 3.8, 10 x 1000 3.8 / 4.1),
+// unless the last tile column has only up to eight nodes (waves with so few
+// active lanes run slower, and 64 x 4 tiles have twice as many: 200^2 4.9 / 3.95,
+// 72^2 4.85 / 4.5, 8 x 1000 5.0 / 3.95).
+template <class St>
+bool small_2byte(int nx, int ny, int cus) {
+  return St::kRef && (nx - 1) % 64 >= 8 && 2 * tiles_total<NearTile<St>>(nx, ny) <= cus;
+}
+
 // One step: NearTile while the 256 MiB memory cache holds source and
 // destination, StepTile beyond.  Measured, us per step, NearTile / StepTile
 // (FP32 on small lattices: 128 x 8): FP32 512^2 4.72 / 5.05, 560^2 5.00 /
@@ -2178,7 +2189,9 @@ void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_i
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   const unsigned long long bytes = (9ull * St::ES + (St::kRef ? 2 : 0)) * nx * ny;
   const bool stream = stream_stores(bytes, (unsigned long long)St::ES * nx, St::kRef ? kCachedAlu : kCachedHbm);
-  if (2 * bytes <= 256ull << 20)
+  if (small_2byte<St>(nx, ny, ctx->cus))
+    launch_step_tiles<St, NearTile<StoreF32>>(ctx, stream, src, dst, ref_in, ref_out);
+  else if (2 * bytes <= 256ull << 20)
     launch_step_tiles<St, NearTile<St>>(ctx, stream, src, dst, ref_in, ref_out);
   else
     launch_step_tiles<St, StepTile<St>>(ctx, stream, src, dst, ref_in, ref_out);

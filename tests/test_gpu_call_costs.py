@@ -175,3 +175,18 @@ def test_flat_2_byte_steps_agree(nx, ny, storage):
     _single(lat, 5)
     assert torch.equal(lat.state(), once) and torch.equal(lat.save_state()[-2 * nx * ny:], ref)
     lat.close()
+
+
+# 2-byte single steps on 64 x 4 and 64 x 8 tiles: last tile columns of 8, 9 and
+# 64 nodes; 128 tiles of 64 x 8 and 132.
+@pytest.mark.parametrize("storage", ["fp16", "bf16"])
+@pytest.mark.parametrize("nx,ny", [(72, 72), (73, 71), (64, 65), (256, 256), (256, 260), (9, 3)])
+def test_small_2_byte_steps_agree(nx, ny, storage):
+    """Four steps, one call at a time, bitwise the four steps of one launch."""
+    rho, lat = _lat(nx, ny, storage)
+    once = lat.step(4).state()
+    ref = lat.save_state()[-2 * nx * ny:]
+    lat.init(rho)
+    _single(lat, 4)
+    assert torch.equal(lat.state(), once) and torch.equal(lat.save_state()[-2 * nx * ny:], ref)
+    lat.close()
