@@ -2391,8 +2391,14 @@ void launch_stepk(lbm_ctx* ctx, const void* src, const StepOuts<S::K>& outs, int
 // thread halves: us per step, two nodes / one, 64^2 6.62 / 5.32, 256^2 7.05 /
 // 5.74, 400^2 9.96 / 8.61, but 450^2 10.3 / 10.7, 512^2 10.9 / 11.0.  A last
 // tile column of up to eight nodes costs the wider tile most: waves with so
-// few active lanes ran the sweep three times slower (70 x 64 12.8 / 5.4).
-bool small_adjoint(const lbm_ctx* ctx) { return tiles_total<AdjTileSmall>(ctx->p.nx, ctx->p.ny) <= 3 * ctx->cus; }
+// few active lanes ran the sweep three times slower (70 x 64 12.8 / 5.4).  Also
+// on lattices one of its tiles wide, which the wider tile sweeps with as many
+// workgroups and half their lanes or more idle (1 x 16000 24.5 / 13.1, 8 x 50000
+// 66 / 34, 32 x 20000 27.6 / 17.7, but 33 x 20000 26.0 / 26.0).
+bool small_adjoint(const lbm_ctx* ctx) {
+  using S = AdjTileSmall;
+  return ctx->p.nx <= S::TX || tiles_total<S>(ctx->p.nx, ctx->p.ny) <= 3 * ctx->cus;
+}
 
 int check_ctx(const lbm_ctx* ctx, bool need_state) {
   if (!ctx) return fail(LBM_EINVAL, "context is NULL");

@@ -140,6 +140,45 @@ def test_strips_of_one_step_agree(nx, ny, storage):
     with_copies.close()
 
 
+def _adjoint(nx, ny, copies=1):
+    """Forward state and adjoint of a lattice and its copies in y, seeded
+    alike; the lattice sized nx x (copies ny)."""
+    _, co = params_pair(nx, ny, tr=0.7)
+    gen = torch.Generator(device="cuda").manual_seed(nx)
+    rho = 0.5 * (co.rho_g + co.rho_l) + 0.02 * (torch.rand((ny, nx), generator=gen, device="cuda") - 0.5)
+    lam = torch.randn((9, ny, nx), generator=gen, device="cuda")
+    lat = pkg.Lattice(nx, copies * ny, tr=0.7).init(rho.repeat(copies, 1))
+    return lat, lat.save_state(), lat.adjoint_seed(lam.repeat(1, copies, 1)), lat.adjoint_buffer()
+
+
+def test_narrow_adjoints_cost_less_than_wider_ones():
+    """An adjoint step on 8 x 20000 against 33 x 20000, two tile columns of 32:
+    0.6 of its cost on 32 x 8 tiles, 1.1 on 64 x 8."""
+    call = []
+    for nx in (8, 33):
+        lat, f, a, b = _adjoint(nx, 20000)
+        sb, ab = L.lbm_checkpoint_bytes(lat.params), L.lbm_adjoint_bytes(lat.params)
+        call.append(lambda lat=lat, f=f, a=a, b=b, sb=sb, ab=ab: L.lbm_adjoint_step(lat.ctx, f, a, b, sb, ab))
+    _assert_ratio(*call, 0.85)
+
+
+# 775 tiles of 32 x 8 in one column; 32 and 33 columns on either side of it.
+@pytest.mark.parametrize("nx,ny", [(1, 200), (3, 200), (32, 200), (33, 200)])
+def test_narrow_adjoints_agree(nx, ny):
+    """One adjoint step of 31 copies in y, more than three small tiles per
+    CU, bitwise the repeated step of one copy; the parameter sums in
+    proportion, to 1e-6 (FP32 sums of two terms, paired alike, then FP64)."""
+    lat, f, a, b = _adjoint(nx, ny)
+    lat.adjoint_step(f, a, b)
+    one, theta = lat.adjoint_get(b), np.array(lat.adjoint_theta())
+    lat.close()
+    lat, f, a, b = _adjoint(nx, ny, 31)
+    lat.adjoint_step(f, a, b)
+    assert torch.equal(lat.adjoint_get(b), one.repeat(1, 31, 1))
+    assert np.abs(np.array(lat.adjoint_theta()) / 31 - theta).max() <= 1e-6 * np.abs(theta).max()
+    lat.close()
+
+
 # Two steps per launch on either side of the lines between 16 x 16, 64 x 16 and
 # 64 x 24 tiles (256 CUs): 2.8 and 3.1 tiles of 16 x 16 per CU; one 64 x 16
 # tile and more; one 64 x 24 tile and more; two 64 x 16 tiles and more.
