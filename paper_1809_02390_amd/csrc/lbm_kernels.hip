@@ -318,6 +318,13 @@ using NearTile =
     std::conditional_t<St::kRef, TileShape<LBM_NEAR_TILE_16>, TileShape<LBM_NEAR_TILE_F32>>;
 using MomTile = TileShape<64, 16, 4>;
 
+// Several steps per launch where that is faster; compiled with
+// -DLBM_FUSE_STEPS=0 every call takes single steps.
+#ifndef LBM_FUSE_STEPS
+#define LBM_FUSE_STEPS 1
+#endif
+constexpr bool kFuseSteps = LBM_FUSE_STEPS;
+
 // Division by a launch constant d (d >= 1): quotients of n < 2^31 from one
 // high multiplication by m = floor(2^32 / d) (2^32 - 1 for d = 1), at most
 // one too small, and a correction.
@@ -2202,15 +2209,12 @@ void launch_step(lbm_ctx* ctx, const void* src, void* dst, const uint16_t* ref_i
 // address TY + 8 rows of 36 nx bytes from one base with 32-bit offsets,
 // which bounds the width (about 3.7M nodes); wider lattices take single
 // steps.
-#ifndef LBM_FUSE_STEPS
-#define LBM_FUSE_STEPS 1
-#endif
 using Step2Mid = Tile2Shape<64, 16, 8>;
 static_assert(Step2Mid::TY <= Step2Tile::TY, "the width bound of the large tile covers the other");
 
 bool use_step2(const lbm_ctx* ctx) {
   const unsigned long long band = 36ull * (unsigned long long)ctx->p.nx * (Step2Tile::TY + 8);
-  return LBM_FUSE_STEPS && ctx->p.storage == LBM_FP32 && band < (1ull << 32);
+  return ctx->p.storage == LBM_FP32 && band < (1ull << 32);
 }
 
 // src (time t) -> dst (time t + 2), and mid (time t + 1) if kMid.
@@ -2634,7 +2638,7 @@ int lbm_step(lbm_ctx* ctx, int32_t n) {
   if (int st = set_device(ctx)) return st;
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    if (const int shape = stepk_shape<St, false>(ctx)) {
+    if (const int shape = kFuseSteps ? stepk_shape<St, false>(ctx) : 0) {
       with_stepk(shape, [&](auto tile) {
         using S = decltype(tile);
         // as few launches as K steps each allow, of about equal length; for n
@@ -2656,7 +2660,7 @@ int lbm_step(lbm_ctx* ctx, int32_t n) {
     }
     for (int32_t s = 0; s < n;) {
       const int a = ctx->cur, b = ctx->cur ^ 1;
-      if (std::is_same_v<St, StoreF32> && n - s >= 2 && use_step2(ctx)) {
+      if (kFuseSteps && std::is_same_v<St, StoreF32> && n - s >= 2 && use_step2(ctx)) {
         launch_step2<false>(ctx, ctx->buf[a], nullptr, ctx->buf[b]);
         s += 2;
       } else {
@@ -2787,7 +2791,7 @@ int lbm_step_saved_chain(lbm_ctx* ctx, void* const* bufs, int32_t n) {
     if (!bufs[j] || !bufs[j + 1] || bufs[j] == bufs[j + 1])
       return fail(LBM_EINVAL, "bufs[%d] and bufs[%d] must be two distinct device buffers", j, j + 1);
   if (int st = set_device(ctx)) return st;
-  if (const int shape = stepk_shape<StoreF32, true>(ctx)) {
+  if (const int shape = kFuseSteps ? stepk_shape<StoreF32, true>(ctx) : 0) {
     with_stepk(shape, [&](auto tile) {
       using S = decltype(tile);
       for (int32_t j = 0; j < n;) {
@@ -2807,7 +2811,7 @@ int lbm_step_saved_chain(lbm_ctx* ctx, void* const* bufs, int32_t n) {
   }
   for (int32_t j = 0; j < n;) {
     // two steps per launch where the state two steps on goes to a third buffer
-    if (n - j >= 2 && use_step2(ctx) && bufs[j + 2] != bufs[j]) {
+    if (kFuseSteps && n - j >= 2 && use_step2(ctx) && bufs[j + 2] != bufs[j]) {
       launch_step2<true>(ctx, bufs[j], bufs[j + 1], bufs[j + 2]);
       j += 2;
     } else {
