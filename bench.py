@@ -130,6 +130,20 @@ def _profile(path, n_nodes):
     return t if t.get("kernel_sha") == kernel_source_hash() and t.get("n_nodes") == n_nodes else None
 
 
+def kernel_label(storage, single, n_nodes):
+    """The kernel of a step leg.  The library chooses it by storage, lattice
+    and device, so it is named where a current profile saw it run, and one
+    step per launch where the call asks for it."""
+    if single:
+        return f"step_kernel<{storage.upper()}>, one step per launch"
+    t = _profile(PROFILE_TRAFFIC["step2_f32" if storage == "fp32" else "step_" + storage.replace("fp", "f")], n_nodes)
+    if t is None:
+        return f"as the library chooses for {storage.upper()} and {n_nodes} nodes"
+    name = t["kernel"].strip(":").split("<")[0]
+    return f"{name}<{'F32' if storage == 'fp32' else storage.upper()}>, " + (
+        "two steps per launch" if t["updates_per_node"] == 2 else "one step per launch")
+
+
 def alu_roofline(kernel, n_nodes, mlups):
     """Vector-ALU roofline of a kernel bound by it: the lane-instructions per
     update counted by rocprofv3 times the measured update rate, against the
@@ -214,8 +228,7 @@ def step_leg(pkg, wl, timer, storage, n, steps, warmup, tr=0.7, width=10.0, sing
     kernel = "step2_f32" if two_step else "step_" + storage.replace("fp", "f")
     traffic = measured_traffic(kernel, n * n)
     return d, rho0, {"mlups": mlups, "ms_per_step": round(per, 5),
-                     "kernel": ("march_kernel<F32>, two steps per launch" if two_step
-                                else f"step_kernel<{storage.upper()}>, one step per launch"),
+                     "kernel": kernel_label(storage, single, n * n),
                      "achieved_gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
                      "algorithmic_bytes_per_lu": alg,
                      "traffic": traffic, "alu": alu_roofline(kernel, n * n, mlups)}
