@@ -1,6 +1,7 @@
 """The kernels that only lattices past the caches run, on such lattices with
 partial last tile columns and rows, compared node by node: the two-node tiles
-of the one-step kernel (FP32 256 x 8, 2-byte 128 x 8)."""
+of the one-step kernel (FP32 256 x 8, 2-byte 128 x 8) and the states stored
+and loaded by streamed whole rows."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +48,43 @@ def test_two_node_tiles_match_repeated_lattice(storage):
         assert np.abs(one.double().cpu().numpy() - f).max() <= GATE[storage] * co.rho_l
     small.close()
     large.close()
+
+
+# Streamed by whole rows: rows on 64 bytes and a state above 144 MiB.  2576 =
+# 10 tiles of 256 and 16, 1701 = 212 rows of 8 and 5; 4128 = 64 tiles of 64
+# and 32, 2117 = 132 rows of 16 and 5.
+@pytest.mark.parametrize("nx,ny,storage", [(2576, 1701, "fp32"), (4128, 2117, "fp16"), (4128, 2117, "bf16")])
+def test_streamed_initial_state(nx, ny, storage):
+    """The state at rest, stored by tiles, is that of zero velocities, stored
+    node by node, bit for bit, and within 1e-6 of rho_l (FP32: a dozen
+    roundings of terms up to rho_l) or the storage's gate of the oracle on
+    every node; a bad density is seen at the first and the last node."""
+    es = 4 if storage == "fp32" else 2
+    assert es * nx % 64 == 0 and 2 * 9 * es * nx * ny > 288 << 20
+    _, co = params_pair(nx, ny, tr=0.7)
+    host = wl.uniform_noise(nx, ny, 0.5 * (co.rho_g + co.rho_l), 0.01, seed=nx)
+    rho = torch.as_tensor(host, dtype=torch.float32, device="cuda")
+    zero = torch.zeros_like(rho)
+    lat = pkg.Lattice(nx, ny, tr=0.7, storage=storage)
+    used = 9 * es * nx * ny
+    rest = lat.init(rho).save_state()
+    err = np.abs(lat.state().double().cpu().numpy() - oracle_init(co, host)).max()
+    assert err <= (1e-6 if storage == "fp32" else GATE[storage]) * co.rho_l
+    moving = lat.init(rho, zero, zero).save_state()
+    assert torch.equal(rest[:used], moving[:used])
+    if storage != "fp32":
+        assert torch.equal(rest[-2 * nx * ny:], moving[-2 * nx * ny:])
+    for at in ((0, 0), (ny - 1, nx - 1)):
+        bad = rho.clone()
+        bad[at] = float("nan")
+        with pytest.raises(pkg.LbmError):
+            lat.init(bad)
+    lat.close()
+
+
+def test_streamed_load_is_exported_unchanged():
+    """FP32 2576 x 1701: a loaded state comes back bit for bit."""
+    f = torch.randn((9, 1701, 2576), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    lat = pkg.Lattice(2576, 1701, tr=0.7).set_state(f)
+    assert torch.equal(lat.state(), f)
+    lat.close()
