@@ -1452,12 +1452,10 @@ __global__ __launch_bounds__(InitTile<St>::NTHREADS) void init_rest_kernel(const
   }
 }
 
-// Load a post-streaming state.  FP32 states past the caches with the shift in
-// the loads, so that whole rows are streamed (us against shifted stores:
-// 2400^2 62 / 77, 4096^2 199 / 218, 8192^2 816 / 920); smaller ones with the
-// shift in the stores, which the caches merge (in the loads / in the stores:
-// 760^2 7.3 / 6.75, 1000^2 12.5 / 12.0, 300 x 2800 11.3 / 10.6).
-template <class St, bool kWideAddr, bool kStream>
+// Load a post-streaming state.  kShiftLoads (FP32, launch_set): the shift of
+// the streaming goes into the loads, so that whole rows are stored; else into
+// the stores (put_node).
+template <class St, bool kWideAddr, bool kShiftLoads, bool kStream>
 __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict__ fin, void* __restrict__ dst,
                                                         uint16_t* __restrict__ ref_out, int nx, int ny, Divisor width,
                                                         RefPoly<float> q) {
@@ -1465,7 +1463,7 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
   int x, y;
   if (!flat_node(nx, ny, width, o, x, y)) return;
   const Planes<float> F = planes<float>(fin, (size_t)nx * ny);
-  if constexpr (!St::kRef && kStream) {
+  if constexpr (kShiftLoads) {
     // a permutation: slot (i, x) is f_i of node x + e_i
     const Layout L = state_layout(nx, ny, 4);
     const NodeAddr<4> a = node_addr<4>(x, y, nx, ny, (unsigned)nx);
@@ -1474,7 +1472,7 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       const unsigned from = (kCy[i] == 0 ? a.r0 : (kCy[i] > 0 ? a.rp : a.rm)) + (kCx[i] == 0 ? a.c0 : (kCx[i] > 0 ? a.cp : a.cm));
-      put<true>(ldb<float>(F.p[i], from), base + (size_t)i * L.ps * 4, off);
+      put<kStream>(ldb<float>(F.p[i], from), base + (size_t)i * L.ps * 4, off);
     }
   } else {
     float f[9];
@@ -2461,6 +2459,24 @@ void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const 
   });
 }
 
+// Queue the loaded state f.  FP32 states whose populations the memory cache
+// does not hold beside the caller's take the shift in the loads (us, loads /
+// stores: 1584 x 2392 45.4 / 46.5, 3000 x 8000 325 / 341 and, streamed, 2400^2
+// 62 / 77, 8192^2 816 / 920), smaller ones in the stores, which the caches merge
+// (300 x 2800 11.3 / 10.6, 1000^2 12.5 / 12.0, 1500^2 26.7 / 26.3).
+template <class St>
+void launch_set(const lbm_ctx* ctx, const float* f) {
+  const int nx = ctx->p.nx, ny = ctx->p.ny;
+  with_state_access<St>(ctx, [&](auto wide, auto stream) {
+    with_bool(!St::kRef && 72ull * nx * ny > 256ull << 20, [&](auto loads) {
+      constexpr bool kLoads = !St::kRef && decltype(loads)::value;
+      set_state_kernel<St, decltype(wide)::value, kLoads, kLoads && decltype(stream)::value>
+          <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], nx, ny, make_divisor(nx),
+                                                           ctx->q);
+    });
+  });
+}
+
 // Call fn with the storage policy of the context.
 template <class Fn>
 int with_storage(const lbm_ctx* ctx, Fn&& fn) {
@@ -2593,14 +2609,8 @@ int lbm_set_state(lbm_ctx* ctx, const float* f) {
   if (int st = check_ctx(ctx, false)) return st;
   if (!f) return fail(LBM_EINVAL, "f is NULL");
   if (int st = set_device(ctx)) return st;
-  const int nx = ctx->p.nx, ny = ctx->p.ny;
   int st = with_storage(ctx, [&](auto store) -> int {
-    using St = decltype(store);
-    with_state_access<St>(ctx, [&](auto wide, auto stream) {
-      set_state_kernel<St, decltype(wide)::value, !St::kRef && decltype(stream)::value>
-          <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], nx, ny, make_divisor(nx),
-                                                           ctx->q);
-    });
+    launch_set<decltype(store)>(ctx, f);
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });

@@ -73,9 +73,12 @@ def test_shifted_rows_are_merged_in_the_caches():
     lat.close()
 
 
-# FP32: below and above the size from which states are streamed (row length a
-# multiple of 64 bytes and a state above 144 MiB), and rows off 64 bytes.
-@pytest.mark.parametrize("nx,ny", [(3, 1000), (560, 600), (2064, 2031), (2064, 2040), (2101, 2048)])
+# FP32: below and above 256 MiB of populations and state, from where the loads
+# are shifted instead of the stores; below and above the size from which
+# states are streamed (row length a multiple of 64 bytes and a state above 144
+# MiB), and rows off 64 bytes.
+@pytest.mark.parametrize("nx,ny", [(3, 1000), (560, 600), (1863, 2001), (1864, 2001), (2064, 2031), (2064, 2040),
+                                   (2101, 2048)])
 def test_loaded_states_agree(nx, ny):
     """A loaded state is exported unchanged, and a state at zero velocity
     given as populations equals the initial one, bit for bit."""
