@@ -1482,11 +1482,9 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
   }
 }
 
-// Export the post-streaming state f(t).  Stores at per-lane 64-bit addresses:
-// from uniform bases and a 32-bit offset the 2-byte exports past the caches
-// took 4-6 % longer (FP16, us: 2880^2 85.4 / 79.9, 4097^2 200 / 191, 6000^2
-// 364 / 342; FP32 the same either way).
-template <class St, bool kWideAddr>
+// Export the post-streaming state f(t).  kLaneStores: stores at per-lane 64-bit
+// addresses instead of uniform bases and one 32-bit offset (lbm_get_state).
+template <class St, bool kWideAddr, bool kLaneStores>
 __global__ __launch_bounds__(BLK) void get_state_kernel(const void* __restrict__ src,
                                                         const uint16_t* __restrict__ ref_in, float* __restrict__ fout,
                                                         int nx, int ny, Divisor width, RefPoly<float> q) {
@@ -1503,8 +1501,14 @@ __global__ __launch_bounds__(BLK) void get_state_kernel(const void* __restrict__
   float f[9];
   decode<St>(raw, St::kRef ? ref_in[o] : 0, q, f);
   const size_t N = (size_t)nx * ny;
+  if constexpr (kLaneStores) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) fout[(size_t)i * N + o] = f[i];
+    for (int i = 0; i < 9; ++i) fout[(size_t)i * N + o] = f[i];
+  } else {
+    const OutPlanes<float> F = out_planes<float>(fout, N);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) put<false>(f[i], F.p[i], 4u * o);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2628,14 +2632,19 @@ int lbm_get_state(lbm_ctx* ctx, float* f) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   return with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    auto go = [&](auto wide) {
-      get_state_kernel<St, decltype(wide)::value><<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(
-          ctx->buf[ctx->cur], ctx->ref[ctx->cur], f, nx, ny, make_divisor(nx), ctx->q);
+    auto go = [&](auto wide, auto lane) {
+      get_state_kernel<St, decltype(wide)::value, decltype(lane)::value>
+          <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(ctx->buf[ctx->cur], ctx->ref[ctx->cur], f, nx, ny,
+                                                           make_divisor(nx), ctx->q);
     };
+    // 2-byte states whose populations the memory cache does not hold take
+    // per-lane store addresses (FP16, us, from uniform bases / per lane: 2880^2
+    // 85.4 / 79.9, 4097^2 200 / 191, 6000^2 364 / 342, but 5000 x 1000 47.1 /
+    // 48.8, 640^2 4.9 / 4.8; FP32 the same either way)
     if constexpr (St::kRef)
-      go(std::false_type{});
+      with_bool(36ull * nx * ny > 256ull << 20, [&](auto lane) { go(std::false_type{}, lane); });
     else
-      with_bool(wide_state(nx, ny, 4), go);
+      with_bool(wide_state(nx, ny, 4), [&](auto wide) { go(wide, std::false_type{}); });
     HIP_OK(hipGetLastError());
     return LBM_OK;
   });

@@ -232,3 +232,18 @@ def test_small_2_byte_steps_agree(nx, ny, storage):
     _single(lat, 4)
     assert torch.equal(lat.state(), once) and torch.equal(lat.save_state()[-2 * nx * ny:], ref)
     lat.close()
+
+
+# 2-byte exports below and above 256 MiB of populations.
+@pytest.mark.parametrize("storage", ["fp16", "bf16"])
+@pytest.mark.parametrize("nx,ny", [(2736, 2725), (2736, 2727)])
+def test_exports_agree(nx, ny, storage):
+    """The exported state of a lattice that repeats a smaller one is the
+    repeated export."""
+    k = {2725: 25, 2727: 27}[ny]
+    rho, one = _lat(48, k, storage)
+    f = one.step(1).state()
+    one.close()
+    many = pkg.Lattice(nx, ny, tr=0.7, storage=storage).init(rho.repeat(ny // k, nx // 48))
+    assert torch.equal(many.step(1).state(), f.repeat(1, ny // k, nx // 48))
+    many.close()
