@@ -2250,17 +2250,20 @@ using StepKLast = TileKShape<16, 16, 2>;
 //    154, 700^2 (7.6) 151 / 130 / 160;
 //  - else: 712^2 (7.9) 161 / 171 / 160, 740^2 (8.6) 164 / 167 / 163.
 // Storing every state as well (us for 8 steps): 380^2 (2.3) 31.3 / 32.2 / 38.6,
-// 400^2 (2.4) 35.0 / 33.3 / 41.0; 544^2 (4.5) 47.6 / 50.9 / 44.8, 600^2 (5.6)
-// 53.7 / 52.6 / 59.5, 620^2 (5.9) 54.5 / 58.2 / 68.0, 660^2 (6.9) 64.5 / 64.5 /
-// 71.0.
+// 400^2 (2.4) 35.0 / 33.3 / 41.0.  The two-step kernel streams the state
+// between, and beyond one 64 x 16 tile per CU wins only with rows on 64 bytes:
+// 544^2 (4.5) 47.6 / 50.9 / 44.8, 576^2 (5.1) 51.6 / 51.1 / 45.7, 4064 x 89
+// (6.0) 59.5 / - / 51.4, 640^2 (6.3) 58.7 / 51.7 / 65.6, but 568^2 (5.1) 52.4 /
+// 52.1 / 53.7, 300 x 1200 (5.6) 53.6 / 56.7 / 61.2, 620^2 (5.9) 54.5 / 58.2 /
+// 68.0, 660^2 (6.9) 64.5 / 64.5 / 71.0.
 template <bool kChain>
 int last_tile_limit(const lbm_ctx* ctx) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
   const int mid = tiles_total<Step2Mid>(nx, ny);
-  if (kChain) return mid <= cus ? 23 : 65;
-  if (mid <= cus) return 29;
+  if (mid <= cus) return kChain ? 23 : 29;
+  if (kChain && nx % 16) return 65;
   if (tiles_total<Step2Tile>(nx, ny) <= cus) return 42;
-  return mid <= 2 * cus ? 55 : 85;
+  return mid <= 2 * cus ? 55 : (kChain ? 65 : 85);
 }
 
 // The tile of stepk_kernel (1 .. 4, in the order above), or 0 where the

@@ -186,7 +186,7 @@ def test_narrow_adjoints_agree(nx, ny):
 # 64 x 24 tiles (256 CUs): 2.8 and 3.1 tiles of 16 x 16 per CU; one 64 x 16
 # tile and more; one 64 x 24 tile and more; two 64 x 16 tiles and more.
 @pytest.mark.parametrize("nx,ny", [(432, 432), (448, 448), (512, 512), (520, 520), (600, 600), (608, 608), (6000, 24),
-                                   (100, 3000), (200, 1800), (700, 700), (712, 712)])
+                                   (100, 3000), (200, 1800), (700, 700), (712, 712), (576, 576), (4064, 89)])
 def test_two_step_tiles_agree(nx, ny):
     """Three steps in one call, and as a chain of stored states, bitwise three
     calls of one step."""
