@@ -1331,12 +1331,7 @@ __device__ __forceinline__ void put_node(int x, int y, int nx, int ny, const flo
 
 // One thread per node o of the lattice, in row order; width: make_divisor(nx).
 // These kernels move 40 (init), 72 (set, get) or 80 (adjoint seed) bytes per
-// node and are bound by HBM.  Their store policy is stream_whole, except
-// where put_node stores rows shifted by the streaming and the cached lines
-// merge them better: FP32 initial states with velocities (us, streamed /
-// cached: 2880^2 108 / 93, 3600^2 183 / 144, 8192^2 667 / 651; 2-byte 3200^2
-// 74 / 87, 4096^2 111 / 124, streamed) and loaded 2-byte states (4000^2 188 /
-// 167, 8192^2 766 / 732).
+// node and are bound by HBM.
 constexpr int BLK = 256;
 __device__ __forceinline__ bool flat_node(int nx, int ny, const Divisor& width, unsigned& o, int& x, int& y) {
   o = blockIdx.x * BLK + threadIdx.x;
@@ -1478,7 +1473,7 @@ __global__ __launch_bounds__(BLK) void set_state_kernel(const float* __restrict_
     float f[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) f[i] = ldb<float>(F.p[i], 4u * o);
-    put_node<St, kWideAddr, false>(x, y, nx, ny, f, q, dst, ref_out);
+    put_node<St, kWideAddr, kStream>(x, y, nx, ny, f, q, dst, ref_out);
   }
 }
 
@@ -2129,14 +2124,17 @@ bool stream_stores(unsigned long long bytes, unsigned long long row, unsigned lo
 }
 
 // The same for the kernels of one node per thread that write a whole state
-// (initial, loaded and seeded states): only states past the caches.  Smaller
-// ones are read next by another kernel, and rows shorter than a workgroup
-// share their lines with other rows, which streamed stores then write in
-// parts (us, streamed / cached: FP32 set_state 3 x 100000 17.5 / 7.6, 10 x
-// 34000 8.3 / 5.4, 600^2 4.6 / 4.3; adjoint seed 3 x 100000 23.8 / 8.9, 380^2
-// 3.8 / 3.4; but seed 2048^2 48 / 65, 2400^2 65 / 80).
-bool stream_whole(unsigned long long bytes, unsigned long long row) {
-  return bytes >= 16ull << 20 && stream_stores(bytes, row, kCachedHbm);
+// (initial, loaded and seeded states).  Rows that do not start on 64 bytes share
+// their lines with other rows, which streamed stores write in parts (us,
+// streamed / cached: FP32 set_state 3 x 100000 17.5 / 7.6, 10 x 34000 8.3 / 5.4,
+// 600^2 4.6 / 4.3; adjoint seed 3 x 100000 23.8 / 8.9, 380^2 3.8 / 3.3).  Whole
+// rows are streamed past the caches (seed 2048^2 48 / 65, 2400^2 65 / 80) and,
+// as by the step, up to half the L2s, there from about 7 MiB on (set_state
+// 352 x 380 (4.6 MiB) 3.36 / 3.24, 480^2 (7.9) 3.05 / 3.46, 640^2 (14.1) 3.7 /
+// 4.45, 720^2 (17.8) 5.97 / 5.63; seed 480^2 3.3 / 3.6, 1200 x 300 3.8 / 4.5).
+bool past_caches(unsigned long long bytes, unsigned long long row) { return row % 64 == 0 && 2 * bytes > kCachedHbm; }
+bool stream_rows(unsigned long long bytes, unsigned long long row) {
+  return past_caches(bytes, row) || (row % 64 == 0 && bytes >= 7ull << 20 && bytes < 16ull << 20);
 }
 
 // Call fn with v as std::bool_constant.
@@ -2426,30 +2424,31 @@ int set_device(const lbm_ctx* ctx) {
 // the count fits a grid dimension.
 unsigned grid1(size_t n) { return static_cast<unsigned>((n + BLK - 1) / BLK); }
 
-// Call fn(wide, stream) for a kernel that writes (or, with stream unused,
-// reads) a whole state: 64-bit addresses for FP32 states above 4 GiB, and the
+// Call fn(wide, stream): 64-bit addresses for FP32 states above 4 GiB, and the
 // store policy.
 template <class St, class Fn>
-void with_state_access(const lbm_ctx* ctx, Fn&& fn) {
-  const int nx = ctx->p.nx, ny = ctx->p.ny;
-  with_bool(stream_whole(9ull * St::ES * nx * ny, (unsigned long long)St::ES * nx), [&](auto stream) {
+void with_state_access(const lbm_ctx* ctx, bool stream, Fn&& fn) {
+  with_bool(stream, [&](auto str) {
     if constexpr (St::kRef)
-      fn(std::false_type{}, stream);
+      fn(std::false_type{}, str);
     else
-      with_bool(wide_state(nx, ny, 4), [&](auto wide) { fn(wide, stream); });
+      with_bool(wide_state(ctx->p.nx, ctx->p.ny, 4), [&](auto wide) { fn(wide, str); });
   });
 }
 
 // Queue the initial state (init_rest_kernel where it streams, at rest, and
-// its tiles' rows fit 32-bit offsets; else init_kernel).
+// its tiles' rows fit 32-bit offsets; else init_kernel).  init_kernel stores
+// rows shifted by the streaming, which the caches merge better in FP32 (with
+// velocities, us, streamed / cached: 2880^2 108 / 93, 3600^2 183 / 144, 8192^2
+// 667 / 651; 2-byte 3200^2 74 / 87, 4096^2 111 / 124).
 template <class St>
 void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const float* uy0) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   const bool rest = !ux0 && !uy0;
   int* const flag = &ctx->host_dev->flag;
-  with_state_access<St>(ctx, [&](auto wide, auto stream) {
+  const unsigned long long row = 9ull * St::ES * nx;
+  with_state_access<St>(ctx, past_caches(row * ny, row / 9), [&](auto wide, auto stream) {
     using S = InitTile<St>;
-    const unsigned long long row = 9ull * St::ES * nx;
     if constexpr (decltype(stream)::value)
       if (rest && row * S::TY < 1ull << 32) {
         const int ntx = tiles_x<S>(nx), nt = tiles_total<S>(nx, ny);
@@ -2466,18 +2465,24 @@ void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const 
   });
 }
 
-// Queue the loaded state f.  FP32 states whose populations the memory cache
-// does not hold beside the caller's take the shift in the loads (us, loads /
-// stores: 1584 x 2392 45.4 / 46.5, 3000 x 8000 325 / 341 and, streamed, 2400^2
-// 62 / 77, 8192^2 816 / 920), smaller ones in the stores, which the caches merge
-// (300 x 2800 11.3 / 10.6, 1000^2 12.5 / 12.0, 1500^2 26.7 / 26.3).
+// Queue the loaded state f.  FP32 states that are streamed (stream_rows), and
+// those whose populations the memory cache does not hold beside the caller's,
+// take the shift in the loads (us, loads / stores: 1584 x 2392 45.4 / 46.5, 3000
+// x 8000 325 / 341, streamed 2400^2 62 / 77, 8192^2 816 / 920), the others in
+// the stores, which the caches merge (300 x 2800 11.3 / 10.6, 1000^2 12.5 /
+// 12.0, 1500^2 26.7 / 26.3).  2-byte states store shifted rows, streamed only
+// near half the L2s (us, streamed / cached: 600^2 (6.2 MiB) 4.0 / 3.85, 760^2
+// (9.9) 5.4 / 5.0, 820^2 (11.5) 6.0 / 6.5, 1000 x 800 (13.7) 6.9 / 7.9, 4 x
+// 100000 (6.9) 9.9 / 7.2; 4000^2 188 / 167, 8192^2 766 / 732).
 template <class St>
 void launch_set(const lbm_ctx* ctx, const float* f) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
-  with_state_access<St>(ctx, [&](auto wide, auto stream) {
-    with_bool(!St::kRef && 72ull * nx * ny > 256ull << 20, [&](auto loads) {
+  const unsigned long long row = (unsigned long long)St::ES * nx, bytes = 9 * row * ny;
+  const bool stream = St::kRef ? row >= 512 && bytes >= 21ull << 19 && bytes < 16ull << 20 : stream_rows(bytes, row);
+  with_state_access<St>(ctx, stream, [&](auto wide, auto str) {
+    with_bool(!St::kRef && (stream || 2 * bytes > 256ull << 20), [&](auto loads) {
       constexpr bool kLoads = !St::kRef && decltype(loads)::value;
-      set_state_kernel<St, decltype(wide)::value, kLoads, kLoads && decltype(stream)::value>
+      set_state_kernel<St, decltype(wide)::value, kLoads, decltype(str)::value && (kLoads || St::kRef)>
           <<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(f, ctx->buf[0], ctx->ref[0], nx, ny, make_divisor(nx),
                                                            ctx->q);
     });
@@ -2857,7 +2862,7 @@ int lbm_adjoint_seed(lbm_ctx* ctx, const float* lam, void* adj) {
   if (!lam || !adj) return fail(LBM_EINVAL, "lam and adj must be device buffers");
   if (int st = set_device(ctx)) return st;
   const int nx = ctx->p.nx, ny = ctx->p.ny;
-  with_bool(stream_whole(44ull * nx * ny, 4ull * nx), [&](auto stream) {
+  with_bool(stream_rows(44ull * nx * ny, 4ull * nx), [&](auto stream) {
     adjoint_seed_kernel<decltype(stream)::value><<<grid1((size_t)nx * ny), BLK, 0, ctx->stream>>>(
         lam, static_cast<float*>(adj), nx, ny, make_divisor(nx));
   });
