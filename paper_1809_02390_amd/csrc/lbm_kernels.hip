@@ -2253,19 +2253,30 @@ using StepKLast = TileKShape<16, 16, 2>;
 // 544^2 (4.5) 47.6 / 50.9 / 44.8, 576^2 (5.1) 51.6 / 51.1 / 45.7, 4064 x 89
 // (6.0) 59.5 / - / 51.4, 640^2 (6.3) 58.7 / 51.7 / 65.6, but 568^2 (5.1) 52.4 /
 // 52.1 / 53.7, 300 x 1200 (5.6) 53.6 / 56.7 / 61.2, 620^2 (5.9) 54.5 / 58.2 /
-// 68.0, 660^2 (6.9) 64.5 / 64.5 / 71.0.
+// 68.0, 660^2 (6.9) 64.5 / 64.5 / 71.0; and on one row of tiles 10000 x 16 (2.4)
+// 31.9 / 34.0.
+// The odd step behind two-step launches finds its instructions cold, which
+// costs it about 2.5 us more than behind stepk_kernel's short loop: n steps in
+// a call (us, 16 x 16 tiles / the two-step kernel), n = 3: 440^2 (3.1) 12.9 /
+// 13.4, 520^2 15.4 / 16.6, 600^2 17.5 / 18.0, 620^2 (5.9) 17.9 / 19.8, 640^2 (6.3)
+// 18.5 / 16.6; n = 5: 440^2 21.1 / 22.1, 540^2 26.2 / 25.5, 600^2 29.6 / 27.2, 620^2
+// 30.0 / 31.1; n = 7: 620^2 42.1 / 42.5.  Not on wide lattices, where the rows of
+// 16 x 16 tiles lie far apart in the launch (n = 3: 1200 x 300 17.9 / 18.7, 2000
+// x 180 20.6 / 19.7, 4064 x 89 26.9 / 18.1).
 template <bool kChain>
-int last_tile_limit(const lbm_ctx* ctx) {
+int last_tile_limit(const lbm_ctx* ctx, int n) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
   const int mid = tiles_total<Step2Mid>(nx, ny);
-  if (mid <= cus) return kChain ? 23 : 29;
+  const bool odd = n % 2 && n < 8 && nx <= 1800;
+  if (mid <= cus) return kChain ? (ny <= 16 ? 31 : 23) : (odd ? 31 : 29);
   if (kChain && nx % 16) return 65;
-  if (tiles_total<Step2Tile>(nx, ny) <= cus) return 42;
-  return mid <= 2 * cus ? 55 : (kChain ? 65 : 85);
+  if (tiles_total<Step2Tile>(nx, ny) <= cus) return !kChain && odd && n == 3 ? 60 : 42;
+  if (mid <= 2 * cus) return !kChain && odd ? 60 : 55;
+  return kChain ? 65 : 85;
 }
 
-// The tile of stepk_kernel (1 .. 4, in the order above), or 0 where the
-// other kernels are faster.  The more steps per launch, the smaller the tile
+// The tile of stepk_kernel (1 .. 4, in the order above) for n steps, or 0 where
+// the other kernels are faster.  The more steps per launch, the smaller the tile
 // has to be for one thread per node of it and its rings; a tile is taken
 // while the lattice gives the CUs one (4 x 4) or two of them.  Measured, us
 // per step, 4 x 4 / 8 x 8 / 32 x 8 / 16 x 16 tiles / without stepk_kernel:
@@ -2285,7 +2296,7 @@ int last_tile_limit(const lbm_ctx* ctx) {
 // 2.2), but 4000 x 40 4.65 / 5.0 (2.9, 2.4), 5500 x 24 4.7 / 4.8 (2.7, 2.7),
 // 16000 x 9 4.95 / 6.3 (3.9, 2.0).
 template <class St, bool kChain>
-int stepk_shape(const lbm_ctx* ctx) {
+int stepk_shape(const lbm_ctx* ctx, int n) {
   const int nx = ctx->p.nx, ny = ctx->p.ny, cus = ctx->cus;
   if (tiles_total<StepKTiny>(nx, ny) <= cus) return 1;
   if (tiles_total<StepKSmall>(nx, ny) <= 2 * cus) return 2;
@@ -2295,7 +2306,7 @@ int stepk_shape(const lbm_ctx* ctx) {
     const bool sparse = t > 3 * cus && 10 * t > 22 * tiles_total<NearTile<St>>(nx, ny);
     return !sparse && 2 * t <= 11 * cus ? 4 : 0;
   } else {
-    return 10 * t <= last_tile_limit<kChain>(ctx) * cus ? 4 : 0;
+    return 10 * t <= last_tile_limit<kChain>(ctx, n) * cus ? 4 : 0;
   }
 }
 
@@ -2665,7 +2676,7 @@ int lbm_step(lbm_ctx* ctx, int32_t n) {
   if (int st = set_device(ctx)) return st;
   int st = with_storage(ctx, [&](auto store) -> int {
     using St = decltype(store);
-    if (const int shape = kFuseSteps ? stepk_shape<St, false>(ctx) : 0) {
+    if (const int shape = kFuseSteps ? stepk_shape<St, false>(ctx, n) : 0) {
       with_stepk(shape, [&](auto tile) {
         using S = decltype(tile);
         // as few launches as K steps each allow, of about equal length; for n
@@ -2818,7 +2829,7 @@ int lbm_step_saved_chain(lbm_ctx* ctx, void* const* bufs, int32_t n) {
     if (!bufs[j] || !bufs[j + 1] || bufs[j] == bufs[j + 1])
       return fail(LBM_EINVAL, "bufs[%d] and bufs[%d] must be two distinct device buffers", j, j + 1);
   if (int st = set_device(ctx)) return st;
-  if (const int shape = kFuseSteps ? stepk_shape<StoreF32, true>(ctx) : 0) {
+  if (const int shape = kFuseSteps ? stepk_shape<StoreF32, true>(ctx, n) : 0) {
     with_stepk(shape, [&](auto tile) {
       using S = decltype(tile);
       for (int32_t j = 0; j < n;) {
