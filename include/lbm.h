@@ -33,7 +33,8 @@
  *  - The library allocates only small scratch inside the context (on the
  *    device reduction partials and the parameter-gradient accumulator,
  *    cleared on the stream at lbm_create; in pinned host memory the words
- *    kernels return results through); lbm_destroy frees it.
+ *    kernels return results through); lbm_destroy frees it.  The words of up
+ *    to 64 contexts share one page, which the process keeps.
  *    Every state, checkpoint and adjoint buffer belongs to the caller.
  */
 #ifndef LBM_H

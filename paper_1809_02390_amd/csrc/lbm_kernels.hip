@@ -2567,7 +2567,6 @@ int lbm_create(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, void* r
   c->t = 0;
   c->stream = (hipStream_t)stream;
   c->nblocks = tiles_total<MomTile>(p->nx, p->ny);
-  
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
   if (p->storage == LBM_FP32)
