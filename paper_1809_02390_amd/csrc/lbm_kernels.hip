@@ -1372,10 +1372,11 @@ __global__ __launch_bounds__(BLK) void init_kernel(const float* __restrict__ rho
 // and its ring go to LDS, and each slot of the pull layout takes its own from
 // there, so that whole aligned rows are stored.  One node per thread
 // (init_kernel) stores rows shifted by the streaming, whose ends share lines
-// with the next workgroup's: FP32 4096^2 152 us against 97, 8192^2 627 / 366,
-// 16384 x 8192 1115 / 906 (tiles of 256 x 8 in 512 threads; 64 x 16: 100, 400,
-// 1147), FP16 4096^2 98 / 58, 16384 x 8192 754 / 696 (64 x 16; 256 x 8: 65,
-// 705).  On lattices the caches hold it gains nothing.
+// with the next workgroup's (us of lbm_init with its wait, one node per thread /
+// by tiles: FP32 4096^2 160 / 107, 8192^2 629 / 378, 16384 x 8192 1324 / 889, in
+// tiles of 256 x 8 in 512 threads; FP16 4096^2 111 / 68, 8192^2 384 / 322, 16384
+// x 8192 768 / 677, in tiles of 64 x 16).  On lattices the caches hold it gains
+// nothing.
 template <int TX_, int TY_, int WY_>
 struct InitShape {
   static constexpr int TX = TX_, TY = TY_, WY = WY_, NPT = TY / WY, LW = TX + 2;

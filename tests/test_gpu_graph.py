@@ -3,8 +3,8 @@ CUDAGraph on the context's stream) and replayed: every replay bitwise equal
 to the same calls made eagerly, with eager work of the program and
 synchronisations between replays.  A graph records the state buffers of the
 captured launches, so the captured lbm_step(n) takes a multiple of 4 steps:
-it then ends on the buffer it started from, whether the lattice runs one
-or two steps per launch."""
+it then ends on the buffer it started from, whatever number of steps the
+lattice takes per launch."""
 import numpy as np
 import pytest
 import torch
@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
                                              (1000, 700, "fp32", 12)])
 def test_graph_replays_match_eager_calls(nx, ny, storage, n):
     """1024 x 384 and 1000 x 700 run two steps per launch (two and six
-    launches per replay), 256 x 256 and the FP16 lattice one step per launch.
+    launches per replay), 256 x 256 and the FP16 lattice up to three.
     Three replays, each checked against an eager lattice advanced by the
     same n steps: the state and the moments (fields and FP64 totals)."""
     _, co = params_pair(nx, ny, tr=0.7)

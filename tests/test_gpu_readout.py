@@ -57,9 +57,10 @@ def test_initial_state_matches_oracle(vel):
 
 @pytest.mark.parametrize("nx,ny,storage", [(2560, 1603, "fp32"), (4096, 2117, "fp16"), (4096, 2117, "bf16")])
 def test_initial_state_by_tiles(nx, ny, storage):
-    """Lattices that stream past the caches, partial last tile rows: the
-    state at rest, stored by tiles, is that of zero velocities, stored node
-    by node, bit for bit; and a bad density is seen."""
+    """Large lattices, partial last tile rows: the state at rest is that of
+    zero velocities, stored node by node, bit for bit; and a bad density is
+    seen.  2-byte states of this size are stored by tiles (whole rows on 64
+    bytes, above 144 MiB); FP32 ones in test_gpu_large_tiles.py."""
     _, rho, _, lat = _lat(nx, ny, storage)
     rho = torch.as_tensor(rho, dtype=torch.float32, device="cuda")
     zero = torch.zeros((ny, nx), device="cuda")

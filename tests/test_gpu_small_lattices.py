@@ -12,8 +12,9 @@ from tests._gpu_helpers import params_pair
 
 pytestmark = pytest.mark.gpu
 
-# 4 x 4 tiles (up to four steps per launch), 8 x 8 (four), 32 x 8 (three),
-# 16 x 16 (two): whole tiles, remainders, lattices thinner than the rings
+# 4 x 4 tiles (up to four steps per launch; also 5 x 500), 8 x 8 (four; also
+# 7 x 3000), 32 x 8 (three), 16 x 16 (two; 559 x 583 in FP32: 64 x 24): whole
+# tiles, remainders, lattices thinner than the rings
 TINY = [(64, 64), (1, 1), (3, 2), (64, 1), (5, 200), (37, 29)]
 SMALL = [(128, 128), (131, 77), (5, 500), (250, 65)]
 WIDE = [(256, 256), (301, 203), (16384, 1), (7, 3000)]

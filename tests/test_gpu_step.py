@@ -52,14 +52,11 @@ def test_set_get_state_roundtrip_is_exact():
 def test_step_parity_ragged(nx, ny, steps):
     """Several tiles and a ragged tail in both directions; 772 x 37 also has
     interior tiles (the fast addressing path) next to edge tiles.  The first
-    chunk of one step runs the one-step kernel: lattices with fewer 256 x 8
-    tiles than CUs run smaller tiles; 1300 x 410 (312 tiles) runs the
-    256 x 8 tiles of the large workloads, with ragged tails; widths that
-    are multiples of 64 address the FP32 state relative to the tile's run:
-    1024 x 256 with the 128 x 8 tiles, 1024 x 512 with the 256 x 8 tiles
-    (256 of them).  The rest runs two steps per launch (64 x 24 tiles on
-    1300 x 410 and 1024 x 512, 64 x 16 on 1024 x 256, 32 x 8 on the
-    others) and one for an odd remainder."""
+    chunk of one step runs the one-step kernel, on 64 x 4 tiles (all these
+    lattices fit the caches; test_gpu_large_tiles.py has the 256 x 8 tiles).
+    The rest runs several steps per launch: 4 x 4 tiles on the smallest, 8 x 8
+    on 772 x 37, 16 x 16 on 1300 x 410, 64 x 16 on 1024 x 256 and 1024 x
+    512."""
     co, rho, ux, uy = droplet_case(nx, ny, seed=nx)
     lat = lattice(nx, ny, rho, ux, uy, tr=0.8)
     f = oracle_init(co, rho, ux, uy)
@@ -91,8 +88,8 @@ def test_step_parity_sheared_droplet():
 @pytest.mark.parametrize("nx,ny", [(1, 1), (1, 64), (3, 2), (2, 5), (64, 1)])
 def test_step_parity_degenerate(nx, ny):
     """Lattices narrower than the stencil: periodic images of a node are its
-    own neighbours.  One step (the one-step kernel), then 19 (two steps per
-    launch on 32 x 8 tiles, and one)."""
+    own neighbours.  One step (the one-step kernel), then 19 (up to four
+    steps per launch on 4 x 4 tiles)."""
     _, co = params_pair(nx, ny, tr=0.7)
     rng = np.random.default_rng(nx * 100 + ny)
     if nx == 1 and ny == 64:
@@ -156,10 +153,10 @@ def test_moments_fields_and_totals():
                                      (300, 200, 6), (37, 29, 5), (5, 200, 3), (64, 1, 4), (3, 2, 5),
                                      (1, 1, 4)])
 def test_two_step_launches_match_single_steps(nx, ny, n):
-    """lbm_step(n) on FP32 lattices runs two steps per launch on 64 x 24
-    tiles (from 4096 x 1024 to 70 x 9000), on 64 x 16 tiles where those
-    give fewer tiles than CUs (512^2, 600 x 583) and on 32 x 8 tiles below
-    (256^2 down to 1 x 1): interior tiles with 32-bit offsets, edge tiles
+    """lbm_step(n) on FP32 lattices runs two steps per launch in marching
+    strips (16384 x 8192), on 64 x 24 tiles (4096 x 1024 and others), 64 x 16
+    (512^2) or 16 x 16 (20000 x 9), and up to four on smaller ones (32 x 8 on
+    256^2, 4 x 4 on 37 x 29): interior tiles with 32-bit offsets, edge tiles
     with wrapped 64-bit addresses, ragged tiles, an odd remainder as one
     single step, a state above 4 GiB, and lattices thinner than the loaded
     region, down to one node, where it wraps more than once: bitwise the
@@ -178,8 +175,8 @@ def test_two_step_launches_match_single_steps(nx, ny, n):
 
 @pytest.mark.parametrize("nx,ny", [(1000, 700), (512, 512), (300, 200)])
 def test_two_step_chain_matches_single_steps(nx, ny):
-    """lbm_step_saved_chain over distinct buffers (two steps per launch,
-    the state between them written too; 64 x 24, 64 x 16 and 32 x 8 tiles)
+    """lbm_step_saved_chain over distinct buffers (several steps per launch,
+    the states between them written too; 64 x 24, 64 x 16 and 32 x 8 tiles)
     and over alternating buffers (one step per launch): bitwise
     lbm_step_saved, step by step."""
     n = 5
@@ -214,8 +211,8 @@ NONDEFAULT = dict(s_p=0.8, s_eps=1.4, varpi=0.12, a=0.5, b=2.5, r_gas=1.5, tr=0.
 @pytest.mark.parametrize("nx,ny", [(200, 70), (1024, 384)])
 def test_step_parity_nondefault_parameters(nx, ny):
     """Parity at NONDEFAULT after one step (the one-step kernel) and after
-    five more (two steps per launch, then one) on 200 x 70 (32 x 8 tiles)
-    and 1024 x 384 (64 x 24 tiles, one per CU)."""
+    five more: 200 x 70 (up to four steps per launch, 8 x 8 tiles) and 1024
+    x 384 (two, 64 x 24 tiles, one per CU)."""
     _, co = params_pair(nx, ny, **NONDEFAULT)
     rho = wl.droplets(nx, ny, co.rho_g, co.rho_l, co.width, [(nx * 0.45, ny * 0.55)], [min(nx, ny) * 0.3])
     rng = np.random.default_rng(nx)
