@@ -64,7 +64,7 @@ def test_short_rows_are_not_stored_in_parts():
 
 def test_shifted_rows_are_merged_in_the_caches():
     """3600^2: an initial state with velocities (48 bytes per node) against
-    loading a state (72); cached 0.92 of its cost, streamed 1.16."""
+    loading a state (72); cached 0.82 of its cost, streamed 1.16."""
     n = 3600
     rho, lat = _lat(n, n)
     u = torch.full_like(rho, 0.01)
