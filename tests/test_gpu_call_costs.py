@@ -165,20 +165,22 @@ def test_narrow_adjoints_cost_less_than_wider_ones():
     _assert_ratio(*call, 0.85)
 
 
-# 775 tiles of 32 x 8 in one column; 32 and 33 columns on either side of it.
-@pytest.mark.parametrize("nx,ny", [(1, 200), (3, 200), (32, 200), (33, 200)])
-def test_narrow_adjoints_agree(nx, ny):
-    """One adjoint step of 31 copies in y, more than three small tiles per
-    CU, bitwise the repeated step of one copy; the parameter sums in
-    proportion, to 1e-6 (FP32 sums of two terms, paired alike, then FP64)."""
+# 775 tiles of 32 x 8 in one column, lattices 32 and 33 wide on either side of
+# it; and a state above 4 GiB, read relative to each tile's row band and, in
+# the tile rows that wrap, with 64-bit addresses.
+@pytest.mark.parametrize("nx,ny,copies", [(1, 200, 31), (3, 200, 31), (32, 200, 31), (33, 200, 31), (32, 1900, 2000)])
+def test_narrow_adjoints_agree(nx, ny, copies):
+    """One adjoint step of copies in y, more than three small tiles per CU,
+    bitwise the repeated step of one copy; the parameter sums in proportion,
+    to 1e-6 (FP32 sums of two terms, paired alike, then FP64)."""
     lat, f, a, b = _adjoint(nx, ny)
     lat.adjoint_step(f, a, b)
     one, theta = lat.adjoint_get(b), np.array(lat.adjoint_theta())
     lat.close()
-    lat, f, a, b = _adjoint(nx, ny, 31)
+    lat, f, a, b = _adjoint(nx, ny, copies)
     lat.adjoint_step(f, a, b)
-    assert torch.equal(lat.adjoint_get(b), one.repeat(1, 31, 1))
-    assert np.abs(np.array(lat.adjoint_theta()) / 31 - theta).max() <= 1e-6 * np.abs(theta).max()
+    assert torch.equal(lat.adjoint_get(b), one.repeat(1, copies, 1))
+    assert np.abs(np.array(lat.adjoint_theta()) / copies - theta).max() <= 1e-6 * np.abs(theta).max()
     lat.close()
 
 
