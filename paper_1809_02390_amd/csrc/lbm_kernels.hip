@@ -2483,14 +2483,18 @@ void launch_init(const lbm_ctx* ctx, const float* rho0, const float* ux0, const 
 // x 8000 325 / 341, streamed 2400^2 62 / 77, 8192^2 816 / 920), the others in
 // the stores, which the caches merge (300 x 2800 11.3 / 10.6, 1000^2 12.5 /
 // 12.0, 1500^2 26.7 / 26.3).  2-byte states store shifted rows, streamed only
-// near half the L2s (us, streamed / cached: 600^2 (6.2 MiB) 4.0 / 3.85, 760^2
-// (9.9) 5.4 / 5.0, 820^2 (11.5) 6.0 / 6.5, 1000 x 800 (13.7) 6.9 / 7.9, 4 x
-// 100000 (6.9) 9.9 / 7.2; 4000^2 188 / 167, 8192^2 766 / 732).
+// in two ranges of sizes and not short ones (us, streamed / cached: 760^2 (9.9
+// MiB) 5.4 / 5.0, 820^2 (11.5) 6.0 / 6.5, 1000 x 800 (13.7) 6.9 / 7.9, 4 x 100000
+// (6.9) 9.9 / 7.2; 4000^2 188 / 167, 8192^2 766 / 732; with the step and the
+// export behind, 440^2 (3.3) 13.4 / 13.4, 500^2 (4.3) 14.5 / 15.1, 600^2 (6.2)
+// 18.5 / 19.6, 660^2 (7.5) 21.0 / 20.6, 760^2 25.4 / 23.1).
 template <class St>
 void launch_set(const lbm_ctx* ctx, const float* f) {
   const int nx = ctx->p.nx, ny = ctx->p.ny;
   const unsigned long long row = (unsigned long long)St::ES * nx, bytes = 9 * row * ny;
-  const bool stream = St::kRef ? row >= 512 && bytes >= 21ull << 19 && bytes < 16ull << 20 : stream_rows(bytes, row);
+  const unsigned long long half = bytes >> 19;  // half MiB
+  const bool stream =
+      St::kRef ? row >= 512 && ((half >= 8 && half < 14) || (half >= 21 && half < 32)) : stream_rows(bytes, row);
   with_state_access<St>(ctx, stream, [&](auto wide, auto str) {
     with_bool(!St::kRef && (stream || 2 * bytes > 256ull << 20), [&](auto loads) {
       constexpr bool kLoads = !St::kRef && decltype(loads)::value;
